@@ -8,6 +8,8 @@
 //                          SampleExtract; one wave per ciphertext (N <= 1024)
 //   blind_rotate_split_kernel  the same with two waves per ciphertext, each
 //                          computing one half of every transform (N = 2048)
+//   blind_rotate_team_kernel, blind_rotate_split_team_kernel  the same with a
+//                          block per ciphertext, for small batches
 //   keyswitch_init_kernel, keyswitch_mfma_kernel  LWE key switching back to
 //                          dimension n for t = 8, base 4: (0, b), then an exact
 //                          int8 product on the matrix cores added to it
@@ -1126,6 +1128,454 @@ __global__ __launch_bounds__((BrSplitCfg<LOGN, S, WPB, SW>::THREADS),
   }
 }
 
+// --------------------------------------- blind rotation, a team per ciphertext
+// One block per ciphertext, for batches that leave most of the chip idle with
+// one wave each: the 2l digit polynomials of a CMux are transformed side by
+// side, one per T lanes ("slot"), and left in LDS; after a barrier slot o < O
+// forms output o (polynomial o / 2, key part o % 2) from all of them, inverts
+// it and adds the rounded words to the accumulator with LDS atomics; a second
+// barrier ends the CMux.
+// A CMux of the one-wave kernel is one chain of 2l + 4 transforms with the
+// SIMD to itself: 33,000 clocks at N = 1024, l = 3, of which 15,000 issue
+// arithmetic (a lone wave issues a 32-bit instruction every 8 clocks and LDS
+// writes at 38 bytes per clock).  Here the chain is one forward and one
+// inverse transform and 2l products: 9,900 clocks (digits 640, forward 2250,
+// its write and the wait for the two waves that share a SIMD 1600, products
+// 2000, inverse 1900, update 1300).  Up to 256 gates at n = 630: 8.95 ->
+// 2.65 ms; 16 gates at n = 64, N = 256: 0.72 -> 0.18 ms.  What bounds it is
+// LDS traffic (about 5900 clocks of it per CMux, two thirds of them writes,
+// which run at 80 bytes per clock against 250 for reads) at six waves in step.
+// The key is requested up to one CMux ahead, a row at a time between other
+// work: 24 loads in a row held their wave up for 900 clocks, and rows
+// requested when needed for 1500.
+template <int LOGN, int L>
+struct BrTeamCfg {
+  using Lay = RingLayout<LOGN, 2>;
+  static constexpr int NR = 1 << LOGN, NC = Lay::N, E = Lay::E, T = Lay::T;
+  static constexpr int R = 2 * L, O = 4;
+  static constexpr int SLOTS = R > O ? R : O;
+  static constexpr int THREADS = (SLOTS * T + 63) / 64 * 64;
+  static constexpr int SCR = Lay::SCR;
+  static constexpr int COPIES = 3;   // of each accumulator polynomial: [P, -P, P]
+  static constexpr int MAX_N = 4096;  // rotation amounts held in LDS
+  static constexpr int PF = 3;        // key rows requested one CMux ahead
+  static constexpr int LDS_BYTES =
+      NC * 16 + (NC - 1) * 16 + NC * 16 + 2 * COPIES * NR * 4 + (R + O) * SCR * 16 + MAX_N * 2;
+  // waves per SIMD of the blocks that the LDS lets share a CU
+  static constexpr int MIN_WAVES = 160 * 1024 / LDS_BYTES * (THREADS / 64) > 4 ? 2 : 1;
+  static_assert(LDS_BYTES <= 160 * 1024, "block exceeds the CU's LDS");
+};
+
+template <int LOGN, int L>
+__global__ __launch_bounds__((BrTeamCfg<LOGN, L>::THREADS), (BrTeamCfg<LOGN, L>::MIN_WAVES)) void blind_rotate_team_kernel(
+    const double2* __restrict__ bk, const double2* __restrict__ tw_g, const uint16_t* __restrict__ abar,
+    const uint32_t* __restrict__ testvec, uint32_t* __restrict__ extract, int n, int bg_bit,
+    const uint32_t* __restrict__ acc_in, uint32_t* __restrict__ acc_out) {
+  using C = BrTeamCfg<LOGN, L>;
+  using Lay = typename C::Lay;
+  constexpr int NR = C::NR, NC = C::NC, E = C::E, T = C::T, R = C::R, O = C::O, PF = C::PF < R ? C::PF : R;
+  __shared__ double2 s_tw[NC];
+  __shared__ double2 s_itw[NC - 1];
+  __shared__ double2 s_twist[NC];
+  __shared__ double2 s_x[R][Lay::SCR];    // a slot's transpose scratch, then its transformed digits
+  __shared__ double2 s_inv[O][Lay::SCR];  // transpose scratch of the inverse transforms
+  // the accumulator's polynomials P as [P, -P, P]: coefficient j of X^e P is
+  // word ((-e) mod 2N) + j, so that a lane's rotated words are one base
+  // address plus constants
+  __shared__ uint32_t s_acc[2][C::COPIES * NR];
+  __shared__ uint16_t s_ab[C::MAX_N];  // the rotation amounts
+
+  const int slot = T == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / T) : threadIdx.x / T;
+  const int t = threadIdx.x % T;
+  const int64_t c = blockIdx.x;
+  const uint16_t* ab = abar + c * (n + 1);
+
+  for (int k = threadIdx.x; k < n; k += C::THREADS) s_ab[k] = ab[k];
+  for (int k = threadIdx.x; k < NC; k += C::THREADS) {
+    s_tw[tw_lds_slot<Lay>(k)] = tw_g[k];
+    s_twist[k] = tw_g[2 * NC + k];
+  }
+  for (int k = threadIdx.x; k < NC - 1; k += C::THREADS) s_itw[k] = tw_g[NC + k];
+  {
+    const uint32_t bbar = ab[n];
+    const uint32_t e0 = (2u * NR - bbar) & (2u * NR - 1);
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) {
+      uint32_t va = 0u, vb;
+      if (acc_in != nullptr) {
+        va = acc_in[c * 2 * NR + j];
+        vb = acc_in[c * 2 * NR + NR + j];
+      } else if (testvec == nullptr) {
+        const int src = j - static_cast<int>(e0 & (NR - 1));
+        const uint32_t m = static_cast<uint32_t>(src >> 31) ^ (0u - ((e0 / NR) & 1u));
+        vb = (kMu ^ m) - m;
+      } else {
+        vb = rot_coef<NR>(testvec, e0, j);
+      }
+#pragma unroll
+      for (int k = 0; k < C::COPIES; k++) {
+        s_acc[0][k * NR + j] = k & 1 ? 0u - va : va;
+        s_acc[1][k * NR + j] = k & 1 ? 0u - vb : vb;
+      }
+    }
+  }
+  const PtrTable itw{s_itw};
+
+  // row r = q L + jj of this slot: digit jj of polynomial q.  The offset of
+  // the signed decomposition (half a base in every digit position and the
+  // rounding bit) plus half a base more in this digit's position alone makes
+  // the digit the sign extension of its field (the carry out of the field is
+  // not read)
+  const int q = slot / L, jj = slot % L;
+  const uint32_t half = 1u << (bg_bit - 1);
+  const uint32_t dpos = static_cast<uint32_t>(32 - (jj + 1) * bg_bit), dw = static_cast<uint32_t>(bg_bit);
+  uint32_t offset = half << dpos;
+  for (int j = 1; j <= L; j++) offset += half << (32 - j * bg_bit);
+  if (L * bg_bit < 32) offset += 1u << (31 - L * bg_bit);
+
+  constexpr uint32_t kKeyBytes = static_cast<uint32_t>(R) * O * NC * 16;  // one CMux's key
+  const uint32_t voff = static_cast<uint32_t>(slot * NC + t) * 16u;        // output `slot` of a row
+  // key points of this slot's output: rows [0, PF) are requested one CMux
+  // ahead, row PF once the slot's own transform is done, the others when the
+  // row PF + 1 before them has been used
+  double2 w[R][E];
+  auto fetch = [&](auto RI, __amdgpu_buffer_rsrc_t key) {
+    constexpr int r = decltype(RI)::value;
+    if constexpr (r < R) {
+#pragma unroll
+      for (int e = 0; e < E; e++) w[r][e] = load_b128(key, voff, static_cast<uint32_t>((r * O * NC + e * T) * 16));
+    }
+  };
+  // (past the last CMux a zero-size resource reads nothing)
+  auto key_of = [&](int i) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(bk)) + static_cast<size_t>(i) * kKeyBytes,
+                                             0, i < n ? kKeyBytes : 0u, 0x00020000);
+  };
+  if (slot < O) {
+    const __amdgpu_buffer_rsrc_t key = key_of(0);
+    static_for<0, PF>([&](auto RI) { fetch(RI, key); });
+  }
+  __syncthreads();
+
+  for (int i = 0; i < n; i++) {
+    const uint32_t a_i = s_ab[i];
+    const __amdgpu_buffer_rsrc_t key = key_of(i), key_next = key_of(i + 1);
+    if (R * T == C::THREADS || slot < R) {
+      double2 x[E];
+      const uint32_t* P = s_acc[q] + NR + t;  // -P at this lane's coefficients
+      const uint32_t* Q = s_acc[q] + (static_cast<uint32_t>(t - static_cast<int>(a_i)) & (2 * NR - 1));  // X^{a_i} P
+#pragma unroll
+      for (int e = 0; e < E; e++)
+        x[e] = make_double2(static_cast<double>(signed_field(Q[T * e] + P[T * e] + offset, dpos, dw)),
+                            static_cast<double>(signed_field(Q[T * e + NC] + P[T * e + NC] + offset, dpos, dw)));
+      fft_forward<Lay, true>(x, t, s_x[slot], s_tw, tw_g, 1);
+#pragma unroll
+      for (int e = 0; e < E; e++) s_x[slot][e * T + t] = x[e];
+    }
+    if (slot < O) fetch(std::integral_constant<int, PF>{}, key);
+    __syncthreads();
+    if (slot < O) {
+      double2 acc[1][E], xr[2][E];
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        acc[0][e] = make_double2(0.0, 0.0);
+        xr[0][e] = s_x[0][e * T + t];
+      }
+      static_for<0, R>([&](auto RI) {
+        constexpr int r = decltype(RI)::value;
+        if constexpr (r + 1 < R) {
+#pragma unroll
+          for (int e = 0; e < E; e++) xr[(r + 1) & 1][e] = s_x[r + 1][e * T + t];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < E; e++) cmac(acc[0][e], xr[r & 1][e], w[r][e]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(std::integral_constant<int, r + PF + 1>{}, key);
+      });
+      fetch(std::integral_constant<int, 0>{}, key_next);
+      double2 tau[E];
+#pragma unroll
+      for (int e = 0; e < E; e++) tau[e] = s_twist[t + T * e];
+      __builtin_amdgcn_sched_barrier(0);
+      fft_inverse<Lay, 0, 1>(acc, t, s_inv[slot], itw);
+      uint32_t* P = s_acc[slot / 2];
+      const uint32_t sh = (slot & 1) * 16u;
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        const int j = t + T * e;
+        const double2 v = cmul(acc[0][e], tau[e]);
+        const uint32_t r0 = round_low32(v.x) << sh, r1 = round_low32(v.y) << sh;
+#pragma unroll
+        for (int k = 0; k < C::COPIES; k++) {
+          __hip_atomic_fetch_add(&P[j + k * NR], k & 1 ? 0u - r0 : r0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&P[j + NC + k * NR], k & 1 ? 0u - r1 : r1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        // the next CMux's key rows, spread over the update
+#pragma unroll
+        for (int r = 1; r < PF; r++)
+          w[r][e] = load_b128(key_next, voff, static_cast<uint32_t>((r * O * NC + e * T) * 16));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();
+  }
+
+  if (acc_out != nullptr) {
+    uint32_t* dst = acc_out + c * 2 * NR;
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) {
+      dst[j] = s_acc[0][j];
+      dst[NR + j] = s_acc[1][j];
+    }
+  } else {
+    uint32_t* out = extract + c * (NR + 1);
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) out[j] = j == 0 ? s_acc[0][0] : 0u - s_acc[0][NR - j];
+    if (threadIdx.x == 0) out[NR] = s_acc[1][0];
+  }
+}
+
+// The same with split transforms (a transform spans two waves, as in
+// blind_rotate_split_kernel): wave 2 r + h computes half h of the transform of
+// digit polynomial r, wave 2 o + h the products, the inverse and the last
+// inverse stage's slice of output o.  (The tables fill the LDS: the rows'
+// space serves the inverse transforms too, after one more barrier.)  A CMux
+// takes 15,400 clocks against 34,500 of the two-wave kernel alone on its CU;
+// up to 256 lookups at n = 750 11.0 -> 4.9 ms.  Bounds: LDS traffic (about
+// 10,000 clocks) and the 880 vector instructions of each of the two waves on
+// a SIMD; without its key loads it would take 14,800.
+template <int LOGN, int L>
+struct BrSplitTeamCfg {
+  using Lay = RingLayout<LOGN, 2>;
+  using Sub = Layout<Lay::LOGN - 1, Lay::LOGE>;
+  static_assert(Lay::T == 128 && Sub::T == 64, "two waves per transform");
+  static constexpr int NR = 1 << LOGN, NC = Lay::N, HN = Sub::N, E = Sub::E;
+  static constexpr int R = 2 * L, O = 4;
+  static_assert(R <= O, "one wave pair per output");
+  static constexpr int THREADS = 2 * O * 64;
+  static constexpr int COPIES = 2;
+  static constexpr int LDS_BYTES = 2 * HN * 16 + (NC - 1) * 16 + NC * 16 + 2 * O * Sub::SCR * 16 + 2 * COPIES * NR * 4 + 4096 * 2;
+  static_assert(LDS_BYTES <= 160 * 1024, "block exceeds the CU's LDS");
+};
+
+template <int LOGN, int L>
+__global__ __launch_bounds__((BrSplitTeamCfg<LOGN, L>::THREADS), 2) void blind_rotate_split_team_kernel(
+    const double2* __restrict__ bk, const double2* __restrict__ tw_g, const uint16_t* __restrict__ abar,
+    const uint32_t* __restrict__ testvec, uint32_t* __restrict__ extract, int n, int bg_bit,
+    const uint32_t* __restrict__ acc_in, uint32_t* __restrict__ acc_out) {
+  using C = BrSplitTeamCfg<LOGN, L>;
+  using Sub = typename C::Sub;
+  constexpr int NR = C::NR, NC = C::NC, HN = C::HN, E = C::E, R = C::R, O = C::O;
+  constexpr int TOP = C::Lay::LOGN - 1;  // the splitting stage
+  __shared__ double2 s_tw[2 * HN];
+  __shared__ double2 s_itw[NC - 1];
+  __shared__ double2 s_twist[NC];
+  __shared__ double2 s_x[2 * O][Sub::SCR];  // a wave's transpose scratch; its half of a transformed row; its slice
+  __shared__ uint32_t s_acc[2][2 * NR];     // [P, -P]: coefficient j of X^e P is word (j - e) mod 2N
+  __shared__ uint16_t s_ab[4096];           // the rotation amounts (n <= 4096)
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = threadIdx.x & 63;
+  const int h = wave & 1, role = wave >> 1;  // half; digit polynomial and output
+  const int64_t c = blockIdx.x;
+  const uint16_t* ab = abar + c * (n + 1);
+
+  for (int k = threadIdx.x; k < n; k += C::THREADS) s_ab[k] = ab[k];
+  for (int k = threadIdx.x; k < 2 * HN; k += C::THREADS) {
+    const int hh = k / HN, m = k % HN;
+    const int top = m > 0 ? 1 << (31 - __builtin_clz(static_cast<unsigned>(m))) : 0;
+    s_tw[hh * HN + tw_lds_slot<Sub>(m)] = tw_g[m + (1 + hh) * top];
+  }
+  for (int k = threadIdx.x; k < NC - 1; k += C::THREADS) s_itw[k] = tw_g[NC + k];
+  for (int k = threadIdx.x; k < NC; k += C::THREADS) s_twist[k] = tw_g[2 * NC + k];
+  {
+    const uint32_t bbar = ab[n];
+    const uint32_t e0 = (2u * NR - bbar) & (2u * NR - 1);
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) {
+      uint32_t va = 0u, vb;
+      if (acc_in != nullptr) {
+        va = acc_in[c * 2 * NR + j];
+        vb = acc_in[c * 2 * NR + NR + j];
+      } else if (testvec == nullptr) {
+        const int src = j - static_cast<int>(e0 & (NR - 1));
+        const uint32_t m = static_cast<uint32_t>(src >> 31) ^ (0u - ((e0 / NR) & 1u));
+        vb = (kMu ^ m) - m;
+      } else {
+        vb = rot_coef<NR>(testvec, e0, j);
+      }
+      s_acc[0][j] = va;
+      s_acc[0][NR + j] = 0u - va;
+      s_acc[1][j] = vb;
+      s_acc[1][NR + j] = 0u - vb;
+    }
+  }
+  const PtrTable itw{s_itw};
+  const double2 tw1 = tw_g[1];
+  const double2 split_w = h ? make_double2(-tw1.x, -tw1.y) : tw1;
+  const double2* tw_half = s_tw + h * HN;
+  double2* scr = s_x[wave];
+
+  // the digit of this wave's row, as in blind_rotate_team_kernel
+  const int q = role / L, jj = role % L;
+  const uint32_t half = 1u << (bg_bit - 1);
+  const uint32_t dpos = static_cast<uint32_t>(32 - (jj + 1) * bg_bit), dw = static_cast<uint32_t>(bg_bit);
+  uint32_t offset = half << dpos;
+  for (int j = 1; j <= L; j++) offset += half << (32 - j * bg_bit);
+  if (L * bg_bit < 32) offset += 1u << (31 - L * bg_bit);
+
+  constexpr uint32_t kKeyBytes = static_cast<uint32_t>(R) * O * NC * 16;  // one CMux's key
+  const uint32_t voff = static_cast<uint32_t>(role * NC + h * 64 + t) * 16u;  // this half of output `role` of a row
+  double2 w[R][E];
+  auto fetch = [&](auto RI, __amdgpu_buffer_rsrc_t key) {
+    constexpr int r = decltype(RI)::value;
+    if constexpr (r < R) {
+#pragma unroll
+      for (int e = 0; e < E; e++) w[r][e] = load_b128(key, voff, static_cast<uint32_t>((r * O * NC + e * 128) * 16));
+    }
+  };
+  // (past the last CMux a zero-size resource reads nothing)
+  auto key_of = [&](int i) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(bk)) + static_cast<size_t>(i) * kKeyBytes,
+                                             0, i < n ? kKeyBytes : 0u, 0x00020000);
+  };
+  {
+    const __amdgpu_buffer_rsrc_t key = key_of(0);
+    static_for<0, R - 1>([&](auto RI) { fetch(RI, key); });
+  }
+  __syncthreads();
+
+  for (int i = 0; i < n; i++) {
+    const uint32_t a_i = s_ab[i];
+    const __amdgpu_buffer_rsrc_t key = key_of(i), key_next = key_of(i + 1);
+    if (R == O || role < R) {
+      const uint32_t* P = s_acc[q] + NR + t;  // -P at this lane's coefficients
+      const uint32_t* Q = s_acc[q];
+      const uint32_t rot = static_cast<uint32_t>(t) - a_i;
+      double2 x[E];
+      // the accumulator words of half the points at a time, requested together
+      static_for<0, 2>([&](auto GI) {
+        constexpr int e0 = decltype(GI)::value * (E / 2);
+        uint32_t d[E / 2][2][2];
+#pragma unroll
+        for (int e = 0; e < E / 2; e++)
+#pragma unroll
+          for (int hh = 0; hh < 2; hh++)
+#pragma unroll
+            for (int im = 0; im < 2; im++) {
+              const int j = 64 * (e0 + e) + hh * HN + im * NC;
+              d[e][hh][im] = Q[(rot + j) & (2 * NR - 1)] + (P[j] + offset);
+            }
+        __builtin_amdgcn_sched_barrier(0x7);
+#pragma unroll
+        for (int e = 0; e < E / 2; e++) {
+          double dg[2][2];
+#pragma unroll
+          for (int hh = 0; hh < 2; hh++)
+#pragma unroll
+            for (int im = 0; im < 2; im++) dg[hh][im] = static_cast<double>(signed_field(d[e][hh][im], dpos, dw));
+          const double2 u = make_double2(dg[0][0], dg[0][1]), v = make_double2(dg[1][0], dg[1][1]);
+          x[e0 + e] = make_double2(fma(split_w.x, v.x, fma(-split_w.y, v.y, u.x)),
+                                   fma(split_w.x, v.y, fma(split_w.y, v.x, u.y)));
+        }
+      });
+      fetch(std::integral_constant<int, R - 1>{}, key);
+      fft_forward<Sub, true>(x, t, scr, tw_half, tw_g, 2 + h);
+#pragma unroll
+      for (int e = 0; e < E; e++) scr[e * 64 + t] = x[e];
+    } else {
+      fetch(std::integral_constant<int, R - 1>{}, key);
+    }
+    __syncthreads();
+    double2 acc[1][E], xr[2][E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      acc[0][e] = make_double2(0.0, 0.0);
+      xr[0][e] = s_x[h][e * 64 + t];
+    }
+    static_for<0, R>([&](auto RI) {
+      constexpr int r = decltype(RI)::value;
+      if constexpr (r + 1 < R) {
+#pragma unroll
+        for (int e = 0; e < E; e++) xr[(r + 1) & 1][e] = s_x[2 * (r + 1) + h][e * 64 + t];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < E; e++) cmac(acc[0][e], xr[r & 1][e], w[r][e]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (R > 1) fetch(std::integral_constant<int, 0>{}, key_next);
+    __syncthreads();  // the rows are read: their space becomes the inverse's scratch
+    fft_inverse<Sub, 0, 1>(acc, t, scr, itw);
+    int t_x = t;
+    asm volatile("" : "+v"(t_x));
+    // the last stage, as in blind_rotate_split_kernel: wave h finishes both
+    // halves for its slice of the points
+    auto finish = [&](auto HI) {
+      constexpr int H = decltype(HI)::value, HE = E / 2;
+      constexpr int MINE = H * HE, OTHER = (1 - H) * HE;
+#pragma unroll
+      for (int e = 0; e < HE; e++) scr[e * 64 + t_x] = acc[0][OTHER + e];
+      double2 tk[HE], tau[2][HE];
+#pragma unroll
+      for (int e = 0; e < HE; e++) {
+        tk[e] = itw(t_x, (1 << TOP) - 1 + 64 * (MINE + e));
+        tau[0][e] = s_twist[t_x + 64 * (MINE + e)];
+        tau[1][e] = s_twist[t_x + 64 * (MINE + e) + HN];
+      }
+      if constexpr (R > 2) fetch(std::integral_constant<int, 1>{}, key_next);
+      __syncthreads();
+      uint32_t* dst = s_acc[role / 2];
+      const uint32_t sh = (role & 1) * 16u;
+      const double2* src = s_x[wave ^ 1];
+      double2 pv[HE];
+#pragma unroll
+      for (int e = 0; e < HE; e++) pv[e] = src[e * 64 + t_x];
+#pragma unroll
+      for (int e = 0; e < HE; e++) {
+        double2 uv[2] = {H ? pv[e] : acc[0][MINE + e], H ? acc[0][MINE + e] : pv[e]};
+        ct_butterfly(uv[0], uv[1], tk[e]);
+#pragma unroll
+        for (int hh = 0; hh < 2; hh++) {
+          const int j = t_x + 64 * (MINE + e) + hh * HN;
+          const double2 v = cmul(uv[hh], tau[hh][e]);
+          const uint32_t r0 = round_low32(v.x) << sh, r1 = round_low32(v.y) << sh;
+          __hip_atomic_fetch_add(&dst[j], r0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&dst[j + NC], r1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&dst[j + NR], 0u - r0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&dst[j + NR + NC], 0u - r1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        // the next CMux's key rows, spread over the update
+        if constexpr (R > 3) {
+          w[2][2 * e] = load_b128(key_next, voff, static_cast<uint32_t>((2 * O * NC + 2 * e * 128) * 16));
+          w[2][2 * e + 1] = load_b128(key_next, voff, static_cast<uint32_t>((2 * O * NC + (2 * e + 1) * 128) * 16));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (h == 0) {
+      asm volatile("; last stage, half 0");
+      finish(std::integral_constant<int, 0>{});
+      asm volatile("; last stage, half 0 done");
+    } else {
+      asm volatile("; last stage, half 1");
+      finish(std::integral_constant<int, 1>{});
+      asm volatile("; last stage, half 1 done");
+    }
+    __syncthreads();
+  }
+
+  if (acc_out != nullptr) {
+    uint32_t* dst = acc_out + c * 2 * NR;
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) {
+      dst[j] = s_acc[0][j];
+      dst[NR + j] = s_acc[1][j];
+    }
+  } else {
+    uint32_t* out = extract + c * (NR + 1);
+    // -A_{N-j} is word 2N - j of [A, -A] for j >= 1, and A_0 word 0
+    for (int j = threadIdx.x; j < NR; j += C::THREADS) out[j] = s_acc[0][(2 * NR - j) & (2 * NR - 1)];
+    if (threadIdx.x == 0) out[NR] = s_acc[1][0];
+  }
+}
+
 // ------------------------------------------------------- key switching
 // Output sample of batch entry c: c itself, or for the activation units the
 // gate's place in the [V][bits] output tensor (forward ReLU: bit
@@ -1828,6 +2278,26 @@ int launch_br_split(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t
   return launch_status("blind_rotate_split_kernel");
 }
 
+template <int LOGN, int L>
+int launch_br_team(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* testvec, int64_t B, hipStream_t st,
+                   const BrIo& io) {
+  using C = BrTeamCfg<LOGN, L>;
+  hipLaunchKernelGGL((blind_rotate_team_kernel<LOGN, L>), dim3(static_cast<unsigned>(B)), dim3(C::THREADS), 0, st,
+                     br_key(ek, io), reinterpret_cast<const double2*>(ek->tw), ws.abar, testvec, ws.extract,
+                     br_steps(ek, io), ek->p.bg_bit, io.acc_in, io.acc_out);
+  return launch_status("blind_rotate_team_kernel");
+}
+
+template <int LOGN, int L>
+int launch_br_split_team(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* testvec, int64_t B,
+                         hipStream_t st, const BrIo& io) {
+  using C = BrSplitTeamCfg<LOGN, L>;
+  hipLaunchKernelGGL((blind_rotate_split_team_kernel<LOGN, L>), dim3(static_cast<unsigned>(B)), dim3(C::THREADS), 0, st,
+                     br_key(ek, io), reinterpret_cast<const double2*>(ek->tw), ws.abar, testvec, ws.extract,
+                     br_steps(ek, io), ek->p.bg_bit, io.acc_in, io.acc_out);
+  return launch_status("blind_rotate_split_team_kernel");
+}
+
 // the part of a launch's buffers after its first `head` ciphertexts
 inline Workspace ws_tail(const tfhe_eval_key* ek, const Workspace& ws, const BrIo& io, int64_t head) {
   return Workspace{ws.abar + head * (br_steps(ek, io) + 1), ws.extract + head * (ek->p.N + 1)};
@@ -1860,6 +2330,19 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
   const int64_t cus = ek->cus > 0 ? ek->cus : 256;
   auto blocks = [&](int64_t b, int cpb) { return (b + cpb - 1) / cpb; };
   if constexpr (T <= 64) {
+    if constexpr (S == 2) {
+      // a team per ciphertext while that is the faster: rounds of one block
+      // per CU at N = 1024 (l = 3, n = 630: 256 gates 2.65 against 8.95 ms with
+      // one-wave blocks, 512 5.05 against 9.0, 768 7.5 against 10.1, 1024
+      // 10.05 against 10.04), of two at 512 (n = 100: 512 gates 0.35 against
+      // 1.42 ms, 1024 1.30 against 1.43) and of four at 256 (n = 64: 1024 gates
+      // 0.32 against 0.72 ms, 2048 0.62 against 0.79, 4096 1.17 against 0.91)
+      constexpr int64_t kPerCu = LOGN == 10 ? 3 : LOGN == 9 ? 4 : 8;
+      if (B <= kPerCu * cus) {
+        if (ek->p.l == 3) return launch_br_team<LOGN, 3>(ek, ws, testvec, B, st, io);
+        if (ek->p.l == 2) return launch_br_team<LOGN, 2>(ek, ws, testvec, B, st, io);
+      }
+    }
     constexpr int C1 = BrCfg<LOGN, S, 1>::CPB;
     if (blocks(B, C1) <= 4 * cus) return launch_br_blocks<LOGN, S, 1>(ek, ws, testvec, B, st, io);
     // full rounds of 8-wave blocks (one per CU); a last round that one-wave
@@ -1872,6 +2355,12 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
     if (int rc = launch_br_blocks<LOGN, S, 8>(ek, ws, testvec, head, st, io)) return rc;
     return launch_br_blocks<LOGN, S, 1>(ek, ws_tail(ek, ws, io, head), testvec, tail, st, io_tail(ek, io, head));
   } else if constexpr (T == 128) {
+    if constexpr (S == 2) {
+      // a team per ciphertext, one block per CU: up to 256 lookups 4.9 against
+      // 11.0 ms (n = 750), 512 9.9 against 12.5; the third round loses to
+      // three one-ciphertext blocks per CU (600 14.8 against 15.2)
+      if (B <= 2 * cus && ek->p.l == 2) return launch_br_split_team<LOGN, 2>(ek, ws, testvec, B, st, io);
+    }
     // blocks of one ciphertext: one wave per SIMD while two per CU hold the
     // batch, else up to three per CU
     auto one_ct = [&](const Workspace& w, int64_t b, const BrIo& bio) {

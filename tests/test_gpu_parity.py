@@ -814,6 +814,32 @@ def test_block_shapes_for_small_batches(torch):
         assert np.array_equal(full[idx], ref_of(idx))
 
 
+@pytest.mark.parametrize("N,l,bg_bit,per_cu", [(256, 3, 7, 8), (256, 2, 9, 8), (512, 3, 7, 4), (512, 2, 9, 4),
+                                               (1024, 3, 7, 3), (1024, 2, 9, 3), (2048, 2, 10, 2)])
+def test_team_blocks_match_wave_blocks(torch, N, l, bg_bit, per_cu):
+    """Batches up to per_cu ciphertexts per CU take a block per ciphertext,
+    one more takes blocks of one or several ciphertexts: the same samples on
+    both sides of the line, and the oracle's at the edges of the batch.  The
+    first rows rotate by 0, N, 2N - 1 and 1 in every CMux."""
+    n = 5
+    params = dict(n=n, N=N, l=l, bg_bit=bg_bit, ks_t=8, ks_basebit=2, alpha_lwe=2 ** -15, alpha_bk=2 ** -25)
+    sk, ek, ok = keys_for(f"team{N}_l{l}", torch, params=params, seed=0x7EA0 + N + l)
+    limit = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(N + l)
+    tv = rng.integers(0, M32, N, dtype=np.uint64).astype(np.uint32)
+    x = rng.integers(0, M32, (limit + 1, n + 1), dtype=np.uint64).astype(np.uint32)
+    step = M32 // (2 * N)
+    x[:4, :n] = np.array([0, N * step, (2 * N - 1) * step, step], np.uint64).astype(np.uint32)[:, None]
+    xd, tvd = tfhe.to_device(x), tfhe.to_device(tv)
+    run = lambda B: tfhe.to_host(tfhe.tfhe_bootstrap_extract_batch(ek, xd[:B], tvd))
+    full = run(limit + 1)
+    for B in (limit, 5, 1):
+        say(f"team blocks N={N} l={l} B={B}")
+        assert np.array_equal(run(B), full[:B]), B
+    idx = np.array([0, 1, 2, 3, limit - 1, limit])
+    assert np.array_equal(full[idx], oracle.bootstrap_no_ks(ok, x[idx], tv))
+
+
 def test_mlp_relu_7680(torch):
     cfg = wl.CONFIGS["mlp_relu"]
     p = cfg["params"]
