@@ -347,6 +347,24 @@ __device__ __forceinline__ uint32_t rot_coef(const uint32_t* p, uint32_t e, int 
   return (v ^ m) - m;
 }
 
+// The rotation difference X^a p - p plus off at coefficient j of an LDS
+// polynomial p of N words, a in [0, 2N), in six instructions and one LDS read: word (j - a) mod
+// N of p, negated when bit log2 N of j - a is set.  `row` is p's LDS address
+// (a multiple of its 4 N bytes, so that the word's offset is or-ed in), rot4
+// is 4 (t - a) for lane t, and j4 is 4 (j - t).
+template <int N>
+__device__ __forceinline__ uint32_t rot_diff(uint32_t row, uint32_t rot4, uint32_t j4, uint32_t p_j, uint32_t off) {
+  typedef __attribute__((address_space(3))) const uint32_t* lds_ptr;
+  const uint32_t src = rot4 + j4;
+  const uint32_t v = *(lds_ptr)((src & (4u * N - 4u)) | row);
+  const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(src << (31 - __builtin_ctz(4u * N))) >> 31);
+  return (v ^ m) + ((off - p_j) - m);
+}
+
+// LDS byte address of a __shared__ object
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+}
 
 // ------------------------------------------------------------ prep kernel
 __device__ __forceinline__ uint16_t mod_switch(uint32_t x, int N) {
@@ -547,7 +565,8 @@ __global__ __launch_bounds__((BrCfg<LOGN, S, WPB>::THREADS), (BrCfg<LOGN, S, WPB
   if constexpr (C::MIN_WAVES == 1) asm volatile("" ::: "a255");
   __shared__ double2 s_tw[NC];
   __shared__ double2 s_scr[CPB * Lay::SCR];
-  __shared__ uint32_t s_acc[CPB * 2 * NR];
+  // (rot_diff needs polynomials at multiples of their size)
+  __shared__ alignas(C::MIN_WAVES == 1 ? 4 * NR : 16) uint32_t s_acc[CPB * 2 * NR];
   __shared__ double2 s_itw[C::ITW_LDS ? NC - 1 : 1];
 
   const int slot = threadIdx.x / T;
@@ -660,13 +679,22 @@ __global__ __launch_bounds__((BrCfg<LOGN, S, WPB>::THREADS), (BrCfg<LOGN, S, WPB
       asm volatile("" : "+v"(a_q), "+v"(t_q));
       // D = X^{a_i} P - P (plus the decomposition offset) at coefficients
       // t + T*e (h = 0) and t + T*e + NR/2 (h = 1): point e's real and imaginary part
+      const uint32_t row_q = lds_address(P);
+      uint32_t rot4 = 4u * (static_cast<uint32_t>(t_q) - a_q);
+      if constexpr (C::MIN_WAVES == 1) asm volatile("" : "+v"(rot4));  // (else the shift moves behind every sum)
       uint32_t D[2][E];
 #pragma unroll
       for (int e = 0; e < E; e++)
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-          const int j = t_q + T * e + h * NC;
-          D[h][e] = (rot_coef<NR>(P, a_q, j) - P[j] + offset) ^ flip;
+          const int j = T * e + h * NC;
+          // (one wave per SIMD issues a 32-bit instruction every 8 clocks: 1024
+          // gates 10.1 -> 9.75 ms with the shorter form, which made blocks of
+          // 8 waves 0.8 % slower)
+          if constexpr (C::MIN_WAVES == 1)
+            D[h][e] = rot_diff<NR>(row_q, rot4, 4u * j, P[t_q + j], offset) ^ flip;
+          else
+            D[h][e] = (rot_coef<NR>(P, a_q, t_q + j) - P[t_q + j] + offset) ^ flip;
         }
       for (int jj = 0; jj < l; jj++) {
         // digit jj is the signed field of bits [32 - (jj+1) bg_bit, 32 - jj bg_bit)
