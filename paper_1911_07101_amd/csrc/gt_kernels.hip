@@ -1764,6 +1764,7 @@ struct KsmGrid {
   int col_tiles;     // nb_total / KSM_NB
   int sample_tiles;  // ceil(B / KSM_SAMPLES)
   int coef_len;      // input coefficients per block, a multiple of KSM_CH
+  bool whole;        // one block per tile covers all of them: it writes the output
 };
 
 // the 2-bit fields of the byte b, one per byte: field f of b in byte f
@@ -1941,7 +1942,11 @@ __global__ __launch_bounds__(KSM_THREADS, 2) void keyswitch_mfma_kernel(const ui
       uint32_t sum = 0u;
 #pragma unroll
       for (int pl = 0; pl < 4; pl++) sum += static_cast<uint32_t>(acc[gi][pl][r]) << (8 * pl);
-      atomicAdd(out + out_index(mode, cs, bits, gate_begin) * row + col, 0u - sum);
+      uint32_t* dst = out + out_index(mode, cs, bits, gate_begin) * row + col;
+      if (g.whole)
+        *dst = (col == n ? in[cs * (N + 1) + N] : 0u) - sum;
+      else
+        atomicAdd(dst, 0u - sum);
     }
   });
 }
@@ -2123,36 +2128,39 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
     int t_q = t;
     asm volatile("" : "+v"(t_q));
     const uint32_t lane_off = static_cast<uint32_t>((t_q * (n + 1) + i) * 4);
-    uint32_t r[2][E];
+    uint32_t r[E];  // the pair of a point, 16 bits each
 #pragma unroll
-    for (int e = 0; e < E; e++)
+    for (int e = 0; e < E; e++) {
+      uint32_t a[2];
 #pragma unroll
       for (int h = 0; h < 2; h++) {
         const uint32_t z_off = static_cast<uint32_t>((T * e + h * NC) * (n + 1) * 4);
-        const uint32_t a = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(lr, lane_off, z_off, 0));
-        r[h][e] = (a + round) >> (32 - prec);
+        a[h] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(lr, lane_off, z_off, 0));
+        a[h] = (a[h] + round) >> (32 - prec);
       }
+      r[e] = a[0] | (a[1] << 16);
+    }
     for (int j = 0; j < t_digits; j++) {
       const uint32_t sh = static_cast<uint32_t>((t_digits - 1 - j) * basebit);
       for (int v = 1; v <= vals; v++) {
         const uint32_t row = static_cast<uint32_t>((j * vals + v - 1) * O * NC) * 16u;
-        // one-wave blocks (the whole register file) request the first
-        // output's key points before the transform; two waves per SIMD have
-        // no registers for them there
+        // the first output's key points are requested before the transform
+        // (with a point's two rounded words in one register there is room for
+        // them at two waves per SIMD too: 8 packings 0.300 -> 0.283 ms, 216
+        // 6.40 -> 6.30 ms; a block barrier per digit or row, which holds the
+        // waves to the same key lines, cost 3 % and 14 %)
         double2 w[E];
-        if constexpr (C::MIN_WAVES == 1) {
 #pragma unroll
-          for (int e = 0; e < E; e++) w[e] = load_b128(kr, voff, row + static_cast<uint32_t>(e * T * 16));
-        }
+        for (int e = 0; e < E; e++) w[e] = load_b128(kr, voff, row + static_cast<uint32_t>(e * T * 16));
         double2 x[E];
 #pragma unroll
         for (int e = 0; e < E; e++)
-          x[e] = make_double2(((r[0][e] >> sh) & static_cast<uint32_t>(vals)) == static_cast<uint32_t>(v) ? 1.0 : 0.0,
-                              ((r[1][e] >> sh) & static_cast<uint32_t>(vals)) == static_cast<uint32_t>(v) ? 1.0 : 0.0);
+          x[e] = make_double2(((r[e] >> sh) & static_cast<uint32_t>(vals)) == static_cast<uint32_t>(v) ? 1.0 : 0.0,
+                              ((r[e] >> (sh + 16)) & static_cast<uint32_t>(vals)) == static_cast<uint32_t>(v) ? 1.0 : 0.0);
         fft_forward<Lay, true>(x, t, scr, s_tw, tw_g, 1);
 #pragma unroll
         for (int o = 0; o < O; o++) {
-          if (o > 0 || C::MIN_WAVES != 1) {
+          if (o > 0) {
 #pragma unroll
             for (int e = 0; e < E; e++) w[e] = load_b128(kr, voff, row + static_cast<uint32_t>((o * E + e) * T * 16));
           }
@@ -2190,8 +2198,27 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
 
 // SampleExtract of coefficients 0 .. K-1 (Section 3.2, step 3): out[b][i] =
 // (a'_0 .. a'_{N-1}, B_i), a'_j = A_{i-j} (j <= i) or -A_{N+i-j} (j > i)
-__global__ __launch_bounds__(256) void sample_extract_kernel(const uint32_t* __restrict__ trlwe, int N, int64_t B,
-                                                             int K, uint32_t* __restrict__ out) {
+// Rings of at least 256 coefficients: a block writes SE_ROWS whole samples, so
+// that the divisions are uniform and taken once a sample.  Memory-bound.
+constexpr int SE_ROWS = 4;
+
+__global__ __launch_bounds__(256) void sample_extract_kernel(const uint32_t* __restrict__ trlwe, int N, uint32_t rows,
+                                                             uint32_t K, uint32_t* __restrict__ out) {
+  for (int q = 0; q < SE_ROWS; q++) {
+    const uint32_t s = blockIdx.x * SE_ROWS + q;
+    if (s >= rows) return;
+    const uint32_t b = s / K;
+    const int i = static_cast<int>(s - b * K);
+    const uint32_t* A = trlwe + static_cast<int64_t>(b) * 2 * N;
+    uint32_t* dst = out + static_cast<int64_t>(s) * (N + 1);
+    for (int j = threadIdx.x; j < N; j += 256) dst[j] = j <= i ? A[i - j] : 0u - A[N + i - j];
+    if (threadIdx.x == 0) dst[N] = A[N + i];
+  }
+}
+
+// Smaller rings: one word per thread
+__global__ __launch_bounds__(256) void sample_extract_words_kernel(const uint32_t* __restrict__ trlwe, int N, int64_t B,
+                                                                   int K, uint32_t* __restrict__ out) {
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t row = N + 1;
   if (idx >= B * K * row) return;
@@ -2486,7 +2513,8 @@ int launch_keyswitch(const tfhe_eval_key* ek, const uint32_t* in, uint32_t* out,
   if (ks_uses_mfma(p)) {
     // split the input coefficients over k blocks per (sample tile, column
     // tile) so that the rounds of resident blocks (two per CU) are full:
-    // the smallest ceil(tiles k / resident) ceil(N / k) for k <= 8
+    // the smallest ceil(tiles k / resident) ceil(N / k) for k <= 8, and whole
+    // sums unless splitting them takes 4 % off that
     const int64_t cus = ek->cus > 0 ? ek->cus : 256;
     KsmGrid g;
     g.nb_total = ksk_mfma_nb(p);
@@ -2494,18 +2522,27 @@ int launch_keyswitch(const tfhe_eval_key* ek, const uint32_t* in, uint32_t* out,
     const int64_t sample_tiles = (B + KSM_SAMPLES - 1) / KSM_SAMPLES;
     g.sample_tiles = static_cast<int>(sample_tiles);
     const int64_t tiles = sample_tiles * g.col_tiles, resident = 2 * cus;
-    int64_t best_k = 1, best = -1;
+    int64_t best_k = 1, best = -1, whole_cost = 0;
     for (int64_t k = 1; k <= 8 && k <= p.N; k++) {
       const int64_t len = (p.N + k - 1) / k, ranges = (p.N + len - 1) / len;
       const int64_t cost = (tiles * ranges + resident - 1) / resident * len;
-      if (best < 0 || cost < best) best = cost, best_k = k;
+      if (best < 0 || cost < best) {
+        if (k > 1 && cost * 25 > whole_cost * 24) continue;
+        best = cost, best_k = k;
+        if (k == 1) whole_cost = cost;
+      }
     }
     g.coef_len = static_cast<int>(((p.N + best_k - 1) / best_k + KSM_CH - 1) / KSM_CH * KSM_CH);
     const int64_t ranges = (p.N + g.coef_len - 1) / g.coef_len;
     const int64_t blocks = tiles * ranges;
-    hipLaunchKernelGGL(keyswitch_init_kernel, dim3(static_cast<unsigned>((B * (p.n + 1) + 255) / 256)), dim3(256), 0,
-                       st, in, out, p.n, p.N, B, mode, bits, gate_begin);
-    if (int rc = launch_status("keyswitch_init_kernel")) return rc;
+    // whole sums are written as they are; partial ones are added to (0, b)
+    // (207,360 samples: 0.22 ms and the additions' traffic less)
+    g.whole = ranges == 1;
+    if (!g.whole) {
+      hipLaunchKernelGGL(keyswitch_init_kernel, dim3(static_cast<unsigned>((B * (p.n + 1) + 255) / 256)), dim3(256), 0,
+                         st, in, out, p.n, p.N, B, mode, bits, gate_begin);
+      if (int rc = launch_status("keyswitch_init_kernel")) return rc;
+    }
     hipLaunchKernelGGL(keyswitch_mfma_kernel, dim3(static_cast<unsigned>(blocks)), dim3(KSM_THREADS), 0, st, in,
                        reinterpret_cast<const i32x4*>(ek->ksk_mfma), out, p.n, p.N, B, mode, bits, gate_begin, g);
   } else if (p.ks_t * (1 << p.ks_basebit) <= 32)
@@ -2631,9 +2668,15 @@ int launch_pack_keyswitch(const tfhe_eval_key* ek, const uint32_t* lwe, int32_t 
 }
 
 int launch_sample_extract(int32_t N, const uint32_t* trlwe, int64_t B, int32_t K, uint32_t* out, void* stream) {
-  const int64_t words = B * K * (N + 1);
-  hipLaunchKernelGGL(sample_extract_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), trlwe, N, B, K, out);
+  const int64_t rows = B * K;  // rows (N + 1) < 2^32
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (N >= 256) {
+    hipLaunchKernelGGL(sample_extract_kernel, dim3(static_cast<unsigned>((rows + SE_ROWS - 1) / SE_ROWS)), dim3(256), 0,
+                       st, trlwe, N, static_cast<uint32_t>(rows), static_cast<uint32_t>(K), out);
+  } else {
+    hipLaunchKernelGGL(sample_extract_words_kernel, dim3(static_cast<unsigned>((rows * (N + 1) + 255) / 256)), dim3(256),
+                       0, st, trlwe, N, B, K, out);
+  }
   return launch_status("sample_extract_kernel");
 }
 
