@@ -1397,7 +1397,9 @@ __global__ __launch_bounds__((BrSplitTeamCfg<LOGN, L>::THREADS), 2) void blind_r
   __shared__ double2 s_itw[NC - 1];
   __shared__ double2 s_twist[NC];
   __shared__ double2 s_x[2 * O][Sub::SCR];  // a wave's transpose scratch; its half of a transformed row; its slice
-  __shared__ uint32_t s_acc[2][2 * NR];     // [P, -P]: coefficient j of X^e P is word (j - e) mod 2N
+  // [P, -P]: coefficient j of X^e P is word (j - e) mod 2N (aligned to its
+  // size: a word's offset is or-ed to its address)
+  __shared__ alignas(8 * NR) uint32_t s_acc[2][2 * NR];
   __shared__ uint16_t s_ab[4096];           // the rotation amounts (n <= 4096)
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1464,6 +1466,8 @@ __global__ __launch_bounds__((BrSplitTeamCfg<LOGN, L>::THREADS), 2) void blind_r
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(bk)) + static_cast<size_t>(i) * kKeyBytes,
                                              0, i < n ? kKeyBytes : 0u, 0x00020000);
   };
+  uint32_t word_mask = 8u * NR - 4u;  // in a vector register: one instruction takes at most one scalar
+  asm volatile("" : "+v"(word_mask));
   {
     const __amdgpu_buffer_rsrc_t key = key_of(0);
     static_for<0, R - 1>([&](auto RI) { fetch(RI, key); });
@@ -1475,35 +1479,26 @@ __global__ __launch_bounds__((BrSplitTeamCfg<LOGN, L>::THREADS), 2) void blind_r
     const __amdgpu_buffer_rsrc_t key = key_of(i), key_next = key_of(i + 1);
     if (R == O || role < R) {
       const uint32_t* P = s_acc[q] + NR + t;  // -P at this lane's coefficients
-      const uint32_t* Q = s_acc[q];
-      const uint32_t rot = static_cast<uint32_t>(t) - a_i;
+      typedef __attribute__((address_space(3))) const uint32_t* lds_ptr;
+      const uint32_t Q = lds_address(s_acc[q]);
+      uint32_t rot4 = 4u * (static_cast<uint32_t>(t) - a_i);
+      asm volatile("" : "+v"(rot4));
       double2 x[E];
-      // the accumulator words of half the points at a time, requested together
-      static_for<0, 2>([&](auto GI) {
-        constexpr int e0 = decltype(GI)::value * (E / 2);
-        uint32_t d[E / 2][2][2];
 #pragma unroll
-        for (int e = 0; e < E / 2; e++)
+      for (int e = 0; e < E; e++) {
+        double dg[2][2];
 #pragma unroll
-          for (int hh = 0; hh < 2; hh++)
+        for (int hh = 0; hh < 2; hh++)
 #pragma unroll
-            for (int im = 0; im < 2; im++) {
-              const int j = 64 * (e0 + e) + hh * HN + im * NC;
-              d[e][hh][im] = Q[(rot + j) & (2 * NR - 1)] + (P[j] + offset);
-            }
-        __builtin_amdgcn_sched_barrier(0x7);
-#pragma unroll
-        for (int e = 0; e < E / 2; e++) {
-          double dg[2][2];
-#pragma unroll
-          for (int hh = 0; hh < 2; hh++)
-#pragma unroll
-            for (int im = 0; im < 2; im++) dg[hh][im] = static_cast<double>(signed_field(d[e][hh][im], dpos, dw));
-          const double2 u = make_double2(dg[0][0], dg[0][1]), v = make_double2(dg[1][0], dg[1][1]);
-          x[e0 + e] = make_double2(fma(split_w.x, v.x, fma(-split_w.y, v.y, u.x)),
-                                   fma(split_w.x, v.y, fma(split_w.y, v.x, u.y)));
-        }
-      });
+          for (int im = 0; im < 2; im++) {
+            const int j = 64 * e + hh * HN + im * NC;
+            const uint32_t D = *(lds_ptr)(((rot4 + 4 * j) & word_mask) | Q) + P[j] + offset;
+            dg[hh][im] = static_cast<double>(signed_field(D, dpos, dw));
+          }
+        const double2 u = make_double2(dg[0][0], dg[0][1]), v = make_double2(dg[1][0], dg[1][1]);
+        x[e] = make_double2(fma(split_w.x, v.x, fma(-split_w.y, v.y, u.x)),
+                            fma(split_w.x, v.y, fma(split_w.y, v.x, u.y)));
+      }
       fetch(std::integral_constant<int, R - 1>{}, key);
       fft_forward<Sub, true>(x, t, scr, tw_half, tw_g, 2 + h);
 #pragma unroll
@@ -2412,9 +2407,12 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
   } else if constexpr (T == 128) {
     if constexpr (S == 2) {
       // a team per ciphertext, one block per CU: up to 256 lookups 4.9 against
-      // 11.0 ms (n = 750), 512 9.9 against 12.5; the third round loses to
-      // three one-ciphertext blocks per CU (600 14.8 against 15.2)
-      if (B <= 2 * cus && ek->p.l == 2) return launch_br_split_team<LOGN, 2>(ek, ws, testvec, B, st, io);
+      // 11.0 ms (n = 750), 512 9.8 against 12.5; a third round when it is two
+      // thirds full (513 15.6 against 15.6 with one-ciphertext blocks, 600 15.4
+      // against 15.1, 700 14.5 against 15.4, 768 14.4 against 16.4)
+      const int64_t third = B - 2 * cus;
+      const bool team = third <= 0 || (third <= cus && 3 * third >= 2 * cus);
+      if (team && ek->p.l == 2) return launch_br_split_team<LOGN, 2>(ek, ws, testvec, B, st, io);
     }
     // blocks of one ciphertext: one wave per SIMD while two per CU hold the
     // batch, else up to three per CU

@@ -815,7 +815,7 @@ def test_block_shapes_for_small_batches(torch):
 
 
 @pytest.mark.parametrize("N,l,bg_bit,per_cu", [(256, 3, 7, 8), (256, 2, 9, 8), (512, 3, 7, 4), (512, 2, 9, 4),
-                                               (1024, 3, 7, 3), (1024, 2, 9, 3), (2048, 2, 10, 2)])
+                                               (1024, 3, 7, 3), (1024, 2, 9, 3), (2048, 2, 10, 2), (2048, 2, 10, 3)])
 def test_team_blocks_match_wave_blocks(torch, N, l, bg_bit, per_cu):
     """Batches up to per_cu ciphertexts per CU take a block per ciphertext,
     one more takes blocks of one or several ciphertexts: the same samples on
