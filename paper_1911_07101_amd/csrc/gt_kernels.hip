@@ -2374,11 +2374,14 @@ inline BrIo io_tail(const tfhe_eval_key* ek, const BrIo& io, int64_t head) {
 // largest block that still gave every CU one: 600 gates 10.31 -> 9.6 ms,
 // 1024 9.64 -> 9.30, 1500 19.55 -> 13.60 (one round of 8-wave blocks instead
 // of two of 4-wave ones), 1000 lookups at N = 2048 27.2 -> 17.0 ms.  A batch
-// whose last round of 8-wave blocks would be partly filled runs that tail as
-// a second launch of one-wave blocks when four per CU hold it (2100 gates
-// 29.9 -> 24.1 ms, 3000 28.8 -> 24.2, 53,760 382.6 -> 378.6; lookups at
-// N = 2048 as one-ciphertext blocks, three per CU: 1102 35.6 -> 30.3 ms,
-// 8292 153.0 -> 148.9).
+// whose last round of 8-wave blocks would be partly filled runs that tail in
+// the shape that a batch of the tail's size takes, when that is a smaller one.
+// One-wave blocks against a partly filled round: 2100 gates 29.9 -> 24.1 ms,
+// 3000 28.8 -> 24.2; at N = 2048 one-ciphertext blocks: 1102 lookups 35.6 ->
+// 30.3.  Teams against those, both on another machine: 2100 gates 25.8 ->
+// 18.5 ms, 2400 25.4 -> 20.8, 2816 26.0 -> 23.7, 3328 29.7 -> 28.2; N = 2048,
+// n = 750, 1280 lookups 29.0 -> 21.8, 1536 29.8 -> 26.6; N = 512, n = 100,
+// 4608 3.89 -> 2.72; N = 256, 8704 3.71 -> 2.59.
 template <int LOGN, int S>
 int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* testvec, int64_t B,
               hipStream_t st, const BrIo& io) {
@@ -2401,15 +2404,26 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
     }
     constexpr int C1 = BrCfg<LOGN, S, 1>::CPB;
     if (blocks(B, C1) <= 4 * cus) return launch_br_blocks<LOGN, S, 1>(ek, ws, testvec, B, st, io);
-    // full rounds of 8-wave blocks (one per CU); a last round that one-wave
-    // blocks hold (four per CU) runs as those instead of as a partly filled
-    // round of 8-wave blocks
+    // up to five ciphertexts per CU at N = 1024: four one-wave blocks per CU,
+    // then a round of teams (l = 3, n = 630: 1025 gates 13.54 -> 12.24 ms with
+    // 8-wave blocks before, 1280 13.60 -> 12.12; two rounds of teams more,
+    // 14.6, would lose to them; l = 2, n = 300: 1280 5.09 -> 4.61)
+    const bool fifth = LOGN == 10 && S == 2 && (ek->p.l == 2 || ek->p.l == 3);
+    if (fifth && B <= 5 * cus) {
+      const int64_t head = 4 * cus;
+      if (int rc = launch_br_blocks<LOGN, S, 1>(ek, ws, testvec, head, st, io)) return rc;
+      return launch_br<LOGN, S>(ek, ws_tail(ek, ws, io, head), testvec, B - head, st, io_tail(ek, io, head));
+    }
+    // full rounds of 8-wave blocks (one per CU); a last round that the shapes
+    // above hold runs as those instead of as a partly filled round of 8-wave
+    // blocks
     const int64_t round = int64_t{BrCfg<LOGN, S, 8>::CPB} * cus;
     const int64_t tail = B % round;
-    if (tail == 0 || blocks(tail, C1) > 4 * cus) return launch_br_blocks<LOGN, S, 8>(ek, ws, testvec, B, st, io);
+    if (tail == 0 || blocks(tail, C1) > (fifth ? 5 : 4) * cus)
+      return launch_br_blocks<LOGN, S, 8>(ek, ws, testvec, B, st, io);
     const int64_t head = B - tail;
     if (int rc = launch_br_blocks<LOGN, S, 8>(ek, ws, testvec, head, st, io)) return rc;
-    return launch_br_blocks<LOGN, S, 1>(ek, ws_tail(ek, ws, io, head), testvec, tail, st, io_tail(ek, io, head));
+    return launch_br<LOGN, S>(ek, ws_tail(ek, ws, io, head), testvec, tail, st, io_tail(ek, io, head));
   } else if constexpr (T == 128) {
     if constexpr (S == 2) {
       // a team per ciphertext, one block per CU: up to 256 lookups 4.9 against
@@ -2422,19 +2436,17 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
     }
     // blocks of one ciphertext: one wave per SIMD while two per CU hold the
     // batch, else up to three per CU
-    auto one_ct = [&](const Workspace& w, int64_t b, const BrIo& bio) {
-      return b <= 2 * cus ? launch_br_split<LOGN, S, 2, 1>(ek, w, testvec, b, st, bio)
-                          : launch_br_split<LOGN, S, 2>(ek, w, testvec, b, st, bio);
-    };
     constexpr int C1 = BrSplitCfg<LOGN, S, 2>::CPB;
-    if (blocks(B, C1) <= 3 * cus) return one_ct(ws, B, io);
-    // as above: a partly filled last round runs as one-ciphertext blocks
+    if (blocks(B, C1) <= 3 * cus)
+      return B <= 2 * cus ? launch_br_split<LOGN, S, 2, 1>(ek, ws, testvec, B, st, io)
+                          : launch_br_split<LOGN, S, 2>(ek, ws, testvec, B, st, io);
+    // as above: a partly filled last round runs as teams or one-ciphertext blocks
     const int64_t round = int64_t{BrSplitCfg<LOGN, S, 8>::CPB} * cus;
     const int64_t tail = B % round;
     if (tail == 0 || blocks(tail, C1) > 3 * cus) return launch_br_split<LOGN, S, 8>(ek, ws, testvec, B, st, io);
     const int64_t head = B - tail;
     if (int rc = launch_br_split<LOGN, S, 8>(ek, ws, testvec, head, st, io)) return rc;
-    return one_ct(ws_tail(ek, ws, io, head), tail, io_tail(ek, io, head));
+    return launch_br<LOGN, S>(ek, ws_tail(ek, ws, io, head), testvec, tail, st, io_tail(ek, io, head));
   } else {
     return launch_br_blocks<LOGN, S, T / 64>(ek, ws, testvec, B, st, io);
   }

@@ -840,6 +840,32 @@ def test_team_blocks_match_wave_blocks(torch, N, l, bg_bit, per_cu):
     assert np.array_equal(full[idx], oracle.bootstrap_no_ks(ok, x[idx], tv))
 
 
+@pytest.mark.parametrize("N,l,bg_bit,round_cu,tails_cu", [(256, 3, 7, 32, (0, 8, 16)), (512, 2, 9, 16, (0, 4, 8)),
+                                                          (1024, 3, 7, 8, (0, 3, 4, 5)), (1024, 2, 9, 8, (0, 3, 4, 5)),
+                                                          (2048, 2, 10, 4, (0, 2, 3))])
+def test_last_round_shapes(torch, N, l, bg_bit, round_cu, tails_cu):
+    """A partly filled last round of large blocks runs as smaller ones: on both
+    sides of each line the samples that full rounds give."""
+    n = 3
+    params = dict(n=n, N=N, l=l, bg_bit=bg_bit, ks_t=8, ks_basebit=2, alpha_lwe=2 ** -15, alpha_bk=2 ** -25)
+    sk, ek, ok = keys_for(f"tail{N}_l{l}", torch, params=params, seed=0x7A11 + N + l)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(N + l)
+    tv = rng.integers(0, M32, N, dtype=np.uint64).astype(np.uint32)
+    x = rng.integers(0, M32, (2 * round_cu * cus, n + 1), dtype=np.uint64).astype(np.uint32)
+    xd, tvd = tfhe.to_device(x), tfhe.to_device(tv)
+    run = lambda B: tfhe.to_host(tfhe.tfhe_bootstrap_extract_batch(ek, xd[:B], tvd))
+    full = run(len(x))
+    for rounds in (0, 1):
+        for tail in tails_cu:
+            for B in ((rounds * round_cu + tail) * cus, (rounds * round_cu + tail) * cus + 1):
+                if B > 0:
+                    say(f"last round N={N} l={l} B={B}")
+                    assert np.array_equal(run(B), full[:B]), B
+    idx = np.array([0, cus, round_cu * cus - 1, round_cu * cus, len(x) - 1])
+    assert np.array_equal(full[idx], oracle.bootstrap_no_ks(ok, x[idx], tv))
+
+
 def test_mlp_relu_7680(torch):
     cfg = wl.CONFIGS["mlp_relu"]
     p = cfg["params"]
