@@ -174,10 +174,15 @@ __device__ __forceinline__ double2 twiddle(int t, const double2* __restrict__ tw
 // signed bit field [pos, pos + width) of x, 0 < width < 32, in one
 // instruction.  Written as inline assembly: the compiler's own bit-field
 // intrinsic has been seen followed by an unsigned int-to-double conversion
-// here, which would turn negative digits positive.
+// here, which would turn negative digits positive.  pos is a scalar, the same
+// for every lane of the wave, or (PER_LANE) each lane's own.
+template <bool PER_LANE = false>
 __device__ __forceinline__ int32_t signed_field(uint32_t x, uint32_t pos, uint32_t width) {
   int32_t r;
-  asm("v_bfe_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(pos), "v"(width));
+  if constexpr (PER_LANE)
+    asm("v_bfe_i32 %0, %1, %2, %3 ; position per lane" : "=v"(r) : "v"(x), "v"(pos), "v"(width));
+  else
+    asm("v_bfe_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(pos), "v"(width));
   return r;
 }
 
@@ -1254,6 +1259,7 @@ __global__ __launch_bounds__((BrTeamCfg<LOGN, L>::THREADS), (BrTeamCfg<LOGN, L>:
   // the digit the sign extension of its field (the carry out of the field is
   // not read)
   const int q = slot / L, jj = slot % L;
+  constexpr bool kOwnPos = T < 64;  // several slots, each with its digit's position, share a wave
   const uint32_t half = 1u << (bg_bit - 1);
   const uint32_t dpos = static_cast<uint32_t>(32 - (jj + 1) * bg_bit), dw = static_cast<uint32_t>(bg_bit);
   uint32_t offset = half << dpos;
@@ -1293,8 +1299,8 @@ __global__ __launch_bounds__((BrTeamCfg<LOGN, L>::THREADS), (BrTeamCfg<LOGN, L>:
       const uint32_t* Q = s_acc[q] + (static_cast<uint32_t>(t - static_cast<int>(a_i)) & (2 * NR - 1));  // X^{a_i} P
 #pragma unroll
       for (int e = 0; e < E; e++)
-        x[e] = make_double2(static_cast<double>(signed_field(Q[T * e] + P[T * e] + offset, dpos, dw)),
-                            static_cast<double>(signed_field(Q[T * e + NC] + P[T * e + NC] + offset, dpos, dw)));
+        x[e] = make_double2(static_cast<double>(signed_field<kOwnPos>(Q[T * e] + P[T * e] + offset, dpos, dw)),
+                            static_cast<double>(signed_field<kOwnPos>(Q[T * e + NC] + P[T * e + NC] + offset, dpos, dw)));
       fft_forward<Lay, true>(x, t, s_x[slot], s_tw, tw_g, 1);
 #pragma unroll
       for (int e = 0; e < E; e++) s_x[slot][e * T + t] = x[e];

@@ -5,6 +5,7 @@ which shares no code with it."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -211,3 +212,46 @@ def test_issue_rate_probe_refuses_bad_arguments():
     assert einval(L.tfhe_probe_valu_rate(0, 4, 0, None, None), "iters")
     assert einval(L.tfhe_probe_valu_rate(0, 4, (1 << 24) + 1, None, None), "iters")
     assert einval(L.tfhe_probe_valu_rate(0, 4, 1, None, None), "NULL")
+
+
+def _device_assembly(tmp_path):
+    """The kernels' gfx950 assembly, made with the build's own flags."""
+    from paper_1911_07101_amd import build as hip_build
+    if not os.path.exists(hip_build.HIPCC):
+        pytest.skip("no hipcc")
+    out = str(tmp_path / "gt_kernels.s")
+    subprocess.run([hip_build.HIPCC, *hip_build.COMMON, "--cuda-device-only", "-S",
+                    os.path.join(hip_build.CSRC, "gt_kernels.hip"), "-o", out], check=True, timeout=600,
+                   stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    return open(out).read()
+
+
+def test_digit_positions_are_scalars_or_declared_per_lane(tmp_path):
+    """Digits are taken by a bit-field extraction in inline assembly.  Where
+    several slots with digits of their own share a wave (teams at N = 256 and
+    512) the field's position differs between lanes: the operand has to be
+    declared a vector register there, since a constraint that asks for a
+    scalar lets the compiler take one lane's position for the whole wave.
+    Every extraction whose position ended up in a vector register says that
+    it is meant to be one."""
+    seen = {"scalar": set(), "per lane": set()}
+    kernel, inline = None, False
+    for line in _device_assembly(tmp_path).splitlines():
+        label = re.match(r"^(_Z\w+):", line)
+        if label:
+            kernel = label.group(1)
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            inline = "#ASMSTART" in line
+        elif inline and "v_bfe_i32" in line:
+            code, _, remark = line.partition(";")
+            position = code.split(None, 1)[1].split(",")[2].strip()
+            if "position per lane" in remark:
+                assert position.startswith("v"), f"{kernel}: {line.strip()}"
+                seen["per lane"].add(kernel)
+            else:
+                assert not position.startswith("v"), f"{kernel}: a scalar position in a vector register: {line.strip()}"
+                seen["scalar"].add(kernel)
+    # log2 N = 8 and 9 with two and three digits; one ring sample's digits per wave from 10 on
+    shared = {f"blind_rotate_team_kernelILi{logn}ELi{l}E" for logn in (8, 9) for l in (2, 3)}
+    assert {m for k in seen["per lane"] for m in re.findall(r"blind_rotate_team_kernelILi\d+ELi\dE", k)} == shared
+    assert any("blind_rotate_team_kernelILi10E" in k for k in seen["scalar"])
