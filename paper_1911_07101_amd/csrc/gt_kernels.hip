@@ -1770,7 +1770,6 @@ struct KsmGrid {
   int col_tiles;     // nb_total / KSM_NB
   int sample_tiles;  // ceil(B / KSM_SAMPLES)
   int coef_len;      // input coefficients per block, a multiple of KSM_CH
-  bool whole;        // one block per tile covers all of them: it writes the output
 };
 
 // the 2-bit fields of the byte b, one per byte: field f of b in byte f
@@ -1785,6 +1784,10 @@ __device__ __forceinline__ int32_t digit_indicator(uint32_t d) {
   return static_cast<int32_t>(__builtin_amdgcn_perm(0u, 1u << (8 * V), d));
 }
 
+// WHOLE: one block per tile covers all input coefficients and writes the
+// output.  (A kernel of its own: a uniform branch in front of every sum cost
+// blocks of partial sums up to 9 % at N = 256, 3 % at N = 1024.)
+template <bool WHOLE>
 __global__ __launch_bounds__(KSM_THREADS, 2) void keyswitch_mfma_kernel(const uint32_t* __restrict__ in,
                                                                      const i32x4* __restrict__ kmf,
                                                                      uint32_t* __restrict__ out, int n, int N,
@@ -1949,7 +1952,7 @@ __global__ __launch_bounds__(KSM_THREADS, 2) void keyswitch_mfma_kernel(const ui
 #pragma unroll
       for (int pl = 0; pl < 4; pl++) sum += static_cast<uint32_t>(acc[gi][pl][r]) << (8 * pl);
       uint32_t* dst = out + out_index(mode, cs, bits, gate_begin) * row + col;
-      if (g.whole)
+      if constexpr (WHOLE)
         *dst = (col == n ? in[cs * (N + 1) + N] : 0u) - sum;
       else
         atomicAdd(dst, 0u - sum);
@@ -2559,14 +2562,16 @@ int launch_keyswitch(const tfhe_eval_key* ek, const uint32_t* in, uint32_t* out,
     const int64_t blocks = tiles * ranges;
     // whole sums are written as they are; partial ones are added to (0, b)
     // (207,360 samples: 0.22 ms and the additions' traffic less)
-    g.whole = ranges == 1;
-    if (!g.whole) {
+    if (ranges == 1) {
+      hipLaunchKernelGGL(keyswitch_mfma_kernel<true>, dim3(static_cast<unsigned>(blocks)), dim3(KSM_THREADS), 0, st, in,
+                         reinterpret_cast<const i32x4*>(ek->ksk_mfma), out, p.n, p.N, B, mode, bits, gate_begin, g);
+    } else {
       hipLaunchKernelGGL(keyswitch_init_kernel, dim3(static_cast<unsigned>((B * (p.n + 1) + 255) / 256)), dim3(256), 0,
                          st, in, out, p.n, p.N, B, mode, bits, gate_begin);
       if (int rc = launch_status("keyswitch_init_kernel")) return rc;
+      hipLaunchKernelGGL(keyswitch_mfma_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(KSM_THREADS), 0, st,
+                         in, reinterpret_cast<const i32x4*>(ek->ksk_mfma), out, p.n, p.N, B, mode, bits, gate_begin, g);
     }
-    hipLaunchKernelGGL(keyswitch_mfma_kernel, dim3(static_cast<unsigned>(blocks)), dim3(KSM_THREADS), 0, st, in,
-                       reinterpret_cast<const i32x4*>(ek->ksk_mfma), out, p.n, p.N, B, mode, bits, gate_begin, g);
   } else if (p.ks_t * (1 << p.ks_basebit) <= 32)
     hipLaunchKernelGGL((keyswitch_kernel<32>), grid, dim3(KS_COLS), 0, st, in, ek->ksk, out, p.n, p.N,
                        p.ks_t, p.ks_basebit, B, mode, bits, gate_begin);

@@ -364,6 +364,68 @@ def test_keyswitch_parity_n750(torch, B):
     assert np.array_equal(got[rows], oracle.keyswitch(ok, x[rows]))
 
 
+def whole_sum_samples(p, cus):
+    """A ragged sample count at which one block per tile covers all input
+    coefficients: its tiles of 128 samples x 64 columns just fill the two
+    resident blocks of every CU, so that splitting them gains nothing (at
+    n = 630 and 256 CUs 51 x 10 tiles of 512)."""
+    col_tiles = (p["n"] + 1 + 63) // 64
+    return 2 * cus // col_tiles * 128 - 123
+
+
+@pytest.mark.parametrize("cfg_name", ["tfhe128_nand", "lut3_n2048", "toy"])
+def test_keyswitch_whole_sums(torch, cfg_name):
+    """A batch whose blocks write whole sums, into an output full of garbage:
+    every row equals the row that smaller batches (partial sums added to an
+    initialised output) give, and spread rows equal the oracle's."""
+    p = wl.CONFIGS[cfg_name]["params"]
+    sk, ek, ok = keys_for(cfg_name, torch)
+    B = whole_sum_samples(p, torch.cuda.get_device_properties(0).multi_processor_count)
+    rng = np.random.default_rng(B)
+    x = rng.integers(0, M32, (B, p["N"] + 1), dtype=np.uint64).astype(np.uint32)
+    x[0, :p["N"]:5] = 0xFFFFFFFF
+    xd = tfhe.to_device(x)
+    out = torch.full((B, p["n"] + 1), 0x5A5A5A5A, dtype=torch.int32, device="cuda:0")
+    say(f"keyswitch whole sums {cfg_name} B={B}")
+    got = tfhe.to_host(tfhe.tfhe_keyswitch_batch(ek, xd, out=out))
+    parts = [tfhe.to_host(tfhe.tfhe_keyswitch_batch(ek, xd[b:b + 96])) for b in range(0, B, 96)]
+    assert np.array_equal(got, np.concatenate(parts))
+    rows = np.unique(np.concatenate([np.linspace(0, B - 1, 60).astype(int), [127, 128, B - 2, B - 1]]))
+    assert np.array_equal(got[rows], oracle.keyswitch(ok, x[rows]))
+
+
+@pytest.mark.parametrize("which", ["relu", "irelu"])
+def test_activation_whole_sums(torch, which):
+    """Forward ReLU and iReLU (toy parameters) with as many gates, in the
+    activations' output orders, into an output full of garbage."""
+    p = wl.CONFIGS["toy"]["params"]
+    sk, ek, ok = keys_for("toy", torch)
+    bits = 5
+    per_value = bits - 1 if which == "relu" else bits
+    V = whole_sum_samples(p, torch.cuda.get_device_properties(0).multi_processor_count) // per_value
+    rng = np.random.default_rng(V)
+    u, d = rng.integers(0, 2, (V, bits)), rng.integers(0, 2, (V, bits))
+    cu = tfhe.tfhe_encrypt_torus(sk, 41, tfhe.encode_bits(u.ravel()), 0).reshape(V, bits, -1)
+    cd = tfhe.tfhe_encrypt_torus(sk, 41, tfhe.encode_bits(d.ravel()), V * bits).reshape(V, bits, -1)
+    out = torch.full((V, bits, p["n"] + 1), 0x5A5A5A5A, dtype=torch.int32, device="cuda:0")
+    say(f"{which} whole sums V={V}")
+    check = np.unique(np.concatenate([np.arange(3), np.linspace(0, V - 1, 20).astype(int)]))
+    if which == "relu":
+        got = tfhe.to_host(tfhe.glyph_relu_batch(ek, tfhe.to_device(cu), bits, y=out))
+        value = u[:, :-1] & (1 - u[:, -1:])
+        assert (got[:, -1, :-1] == 0).all() and (got[:, -1, -1] == M32 - MU).all()
+        gates = got[:, :-1]
+        ref = [oracle.gate_bootstrap(ok, "ANDNY", np.repeat(cu[v, -1:], bits - 1, 0), cu[v, :-1]) for v in check]
+    else:
+        got = tfhe.to_host(tfhe.glyph_irelu_batch(ek, tfhe.to_device(cu), tfhe.to_device(cd), out=out))
+        value = d & (1 - u[:, -1:])
+        gates = got
+        ref = [oracle.gate_bootstrap(ok, "ANDNY", np.repeat(cu[v, -1:], bits, 0), cd[v]) for v in check]
+    assert np.array_equal(gates[check], np.stack(ref))
+    phase = oracle.phase(ok.s, gates.reshape(-1, p["n"] + 1))
+    assert np.array_equal(bits_of(phase), value.ravel())
+
+
 @pytest.mark.parametrize("ks_t,ks_basebit", [(4, 3), (16, 2), (2, 5)])
 def test_keyswitch_parity_other_digit_sizes(torch, ks_t, ks_basebit):
     """The key switch for digit shapes other than t = 8, base 4 (the kernel's
