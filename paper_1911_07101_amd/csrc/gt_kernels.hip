@@ -552,7 +552,8 @@ struct BufTable {
   }
 };
 
-template <int LOGN, int S, int WPB>
+// SHORT_DIFF: the rotation difference by rot_diff (launch_br_blocks)
+template <int LOGN, int S, int WPB, bool SHORT_DIFF>
 __global__ __launch_bounds__((BrCfg<LOGN, S, WPB>::THREADS), (BrCfg<LOGN, S, WPB>::MIN_WAVES)) void blind_rotate_kernel(
     const double2* __restrict__ bk, const double2* __restrict__ tw_g, const uint16_t* __restrict__ abar,
     const uint32_t* __restrict__ testvec, uint32_t* __restrict__ extract, int n, int l, int bg_bit,
@@ -571,7 +572,7 @@ __global__ __launch_bounds__((BrCfg<LOGN, S, WPB>::THREADS), (BrCfg<LOGN, S, WPB
   __shared__ double2 s_tw[NC];
   __shared__ double2 s_scr[CPB * Lay::SCR];
   // (rot_diff needs polynomials at multiples of their size)
-  __shared__ alignas(C::MIN_WAVES == 1 ? 4 * NR : 16) uint32_t s_acc[CPB * 2 * NR];
+  __shared__ alignas(SHORT_DIFF ? 4 * NR : 16) uint32_t s_acc[CPB * 2 * NR];
   __shared__ double2 s_itw[C::ITW_LDS ? NC - 1 : 1];
 
   const int slot = threadIdx.x / T;
@@ -686,17 +687,14 @@ __global__ __launch_bounds__((BrCfg<LOGN, S, WPB>::THREADS), (BrCfg<LOGN, S, WPB
       // t + T*e (h = 0) and t + T*e + NR/2 (h = 1): point e's real and imaginary part
       const uint32_t row_q = lds_address(P);
       uint32_t rot4 = 4u * (static_cast<uint32_t>(t_q) - a_q);
-      if constexpr (C::MIN_WAVES == 1) asm volatile("" : "+v"(rot4));  // (else the shift moves behind every sum)
+      if constexpr (SHORT_DIFF) asm volatile("" : "+v"(rot4));  // (else the shift moves behind every sum)
       uint32_t D[2][E];
 #pragma unroll
       for (int e = 0; e < E; e++)
 #pragma unroll
         for (int h = 0; h < 2; h++) {
           const int j = T * e + h * NC;
-          // (one wave per SIMD issues a 32-bit instruction every 8 clocks: 1024
-          // gates 10.1 -> 9.75 ms with the shorter form, which made blocks of
-          // 8 waves 0.8 % slower)
-          if constexpr (C::MIN_WAVES == 1)
+          if constexpr (SHORT_DIFF)
             D[h][e] = rot_diff<NR>(row_q, rot4, 4u * j, P[t_q + j], offset) ^ flip;
           else
             D[h][e] = (rot_coef<NR>(P, a_q, t_q + j) - P[t_q + j] + offset) ^ flip;
@@ -2325,10 +2323,22 @@ int launch_br_blocks(const tfhe_eval_key* ek, const Workspace& ws, const uint32_
                      hipStream_t st, const BrIo& io) {
   using C = BrCfg<LOGN, S, WPB>;
   const int64_t blocks = (B + C::CPB - 1) / C::CPB;
-  hipLaunchKernelGGL((blind_rotate_kernel<LOGN, S, WPB>), dim3(static_cast<unsigned>(blocks)), dim3(C::THREADS),
-                     0, st, br_key(ek, io), reinterpret_cast<const double2*>(ek->tw), ws.abar, testvec,
-                     ws.extract, br_steps(ek, io), ek->p.l, ek->p.bg_bit, B, io.acc_in, io.acc_out);
-  return launch_status("blind_rotate_kernel");
+  auto launch = [&](auto SHORT_DIFF) {
+    hipLaunchKernelGGL((blind_rotate_kernel<LOGN, S, WPB, decltype(SHORT_DIFF)::value>),
+                       dim3(static_cast<unsigned>(blocks)), dim3(C::THREADS), 0, st, br_key(ek, io),
+                       reinterpret_cast<const double2*>(ek->tw), ws.abar, testvec, ws.extract, br_steps(ek, io),
+                       ek->p.l, ek->p.bg_bit, B, io.acc_in, io.acc_out);
+    return launch_status("blind_rotate_kernel");
+  };
+  // The shorter rotation difference where it is the faster: one wave per SIMD
+  // (a 32-bit instruction every 8 clocks) and more than one digit, from N =
+  // 1024 on (n = 630, l = 3: 1024 gates 10.1 -> 9.75 ms; n = 60, l = 4: 1.20 ->
+  // 1.13).  Blocks of 8 waves lose 0.8 % with it, one digit at N = 1024 up to
+  // 2.8 % (257 samples 0.438 -> 0.450 ms), several ciphertexts per wave at N =
+  // 256 and 512 1 to 2 % (l = 1, 512 samples 0.415 -> 0.424 ms).
+  if constexpr (C::MIN_WAVES == 1 && LOGN >= 10)
+    if (ek->p.l > 1) return launch(std::true_type{});
+  return launch(std::false_type{});
 }
 
 template <int LOGN, int S, int WPB, int SW = 2>
