@@ -2205,20 +2205,27 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
 
 // SampleExtract of coefficients 0 .. K-1 (Section 3.2, step 3): out[b][i] =
 // (a'_0 .. a'_{N-1}, B_i), a'_j = A_{i-j} (j <= i) or -A_{N+i-j} (j > i)
-// Rings of at least 256 coefficients: a block writes SE_ROWS whole samples, so
-// that the divisions are uniform and taken once a sample.  Memory-bound.
-constexpr int SE_ROWS = 4;
-
+// Rings of at least 256 coefficients: a block writes `per_block` whole samples,
+// so that the divisions are uniform and taken once a sample, with the loads
+// of four words per work-item in flight.  Memory-bound (N = 1024, 216 x 1024
+// samples 440 -> 193 us, of which 262 -> 193 by the loads in flight; one
+// sample's loads after the other's took 15 us at N = 4096 for a few samples,
+// 6.5 now).
 __global__ __launch_bounds__(256) void sample_extract_kernel(const uint32_t* __restrict__ trlwe, int N, uint32_t rows,
-                                                             uint32_t K, uint32_t* __restrict__ out) {
-  for (int q = 0; q < SE_ROWS; q++) {
-    const uint32_t s = blockIdx.x * SE_ROWS + q;
+                                                             uint32_t K, int per_block, uint32_t* __restrict__ out) {
+  for (int q = 0; q < per_block; q++) {
+    const uint32_t s = blockIdx.x * per_block + q;
     if (s >= rows) return;
     const uint32_t b = s / K;
     const int i = static_cast<int>(s - b * K);
     const uint32_t* A = trlwe + static_cast<int64_t>(b) * 2 * N;
     uint32_t* dst = out + static_cast<int64_t>(s) * (N + 1);
-    for (int j = threadIdx.x; j < N; j += 256) dst[j] = j <= i ? A[i - j] : 0u - A[N + i - j];
+#pragma unroll 4
+    for (int j = threadIdx.x; j < N; j += 256) {
+      const int src = i - j;  // (A_src, or -A_{N + src}: no branch, so that the loads are in flight together)
+      const uint32_t v = A[src & (N - 1)];
+      dst[j] = src >= 0 ? v : 0u - v;
+    }
     if (threadIdx.x == 0) dst[N] = A[N + i];
   }
 }
@@ -2708,8 +2715,12 @@ int launch_sample_extract(int32_t N, const uint32_t* trlwe, int64_t B, int32_t K
   const int64_t rows = B * K;  // rows (N + 1) < 2^32
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (N >= 256) {
-    hipLaunchKernelGGL(sample_extract_kernel, dim3(static_cast<unsigned>((rows + SE_ROWS - 1) / SE_ROWS)), dim3(256), 0,
-                       st, trlwe, N, static_cast<uint32_t>(rows), static_cast<uint32_t>(K), out);
+    // a sample per block while all blocks are resident at once (8 per CU, 256
+    // CUs) and at N = 4096 (60 x 4096 samples 703 us, four per block 866),
+    // else four (N = 1024, 216 x 1024 samples 193 us, one per block 229)
+    const int per_block = rows <= 2048 || N > 2048 ? 1 : 4;
+    hipLaunchKernelGGL(sample_extract_kernel, dim3(static_cast<unsigned>((rows + per_block - 1) / per_block)), dim3(256),
+                       0, st, trlwe, N, static_cast<uint32_t>(rows), static_cast<uint32_t>(K), per_block, out);
   } else {
     hipLaunchKernelGGL(sample_extract_words_kernel, dim3(static_cast<unsigned>((rows * (N + 1) + 255) / 256)), dim3(256),
                        0, st, trlwe, N, B, K, out);

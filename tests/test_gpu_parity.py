@@ -752,6 +752,25 @@ def test_sample_extract_batch(torch):
             assert np.array_equal(got[b], ref), (N, b)
 
 
+@pytest.mark.parametrize("N,B,K", [(256, 8, 256), (256, 9, 250), (512, 7, 301), (1024, 3, 683), (2048, 1, 2048),
+                                   (2048, 3, 767), (4096, 2, 5), (4096, 1, 2100)])
+def test_sample_extract_block_shapes(torch, N, B, K):
+    """Up to 2048 samples take a block each, as do all at N = 4096, more take
+    blocks of four with a ragged last one: into an output full of garbage,
+    every word against the definition (a'_j = A_{i-j}, or -A_{N+i-j} where
+    j > i)."""
+    rng = np.random.default_rng(N + B + K)
+    acc = rng.integers(0, M32, (B, 2, N), dtype=np.uint64).astype(np.uint32)
+    out = torch.full((B, K, N + 1), 0x5A5A5A5A, dtype=torch.int32, device="cuda:0")
+    say(f"sample extract N={N} B={B} K={K}")
+    got = tfhe.to_host(tfhe.tfhe_sample_extract_batch(tfhe.to_device(acc), K, out=out))
+    i, j = np.arange(K)[:, None], np.arange(N)[None, :]
+    for b in range(B):
+        want = acc[b, 0][(i - j) % N]
+        want = np.where(j <= i, want, (M32 - want.astype(np.uint64)).astype(np.uint32))
+        assert np.array_equal(got[b, :, :N], want) and np.array_equal(got[b, :, N], acc[b, 1, :K]), b
+
+
 def test_bootstrap_onto_multiples_of_inverse_modulus_n2048(torch):
     """Step 4 of the switch with the N = 2048 parameters: a programmable
     bootstrap whose test polynomial holds multiples of 1/q (q = 257) maps
