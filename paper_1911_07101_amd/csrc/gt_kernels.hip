@@ -2205,16 +2205,17 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
 
 // SampleExtract of coefficients 0 .. K-1 (Section 3.2, step 3): out[b][i] =
 // (a'_0 .. a'_{N-1}, B_i), a'_j = A_{i-j} (j <= i) or -A_{N+i-j} (j > i)
-// Rings of at least 256 coefficients: a block writes `per_block` whole samples,
+// Rings of at least 256 coefficients: a block writes PER_BLOCK whole samples,
 // so that the divisions are uniform and taken once a sample, with the loads
 // of four words per work-item in flight.  Memory-bound (N = 1024, 216 x 1024
 // samples 440 -> 193 us, of which 262 -> 193 by the loads in flight; one
 // sample's loads after the other's took 15 us at N = 4096 for a few samples,
 // 6.5 now).
+template <int PER_BLOCK>
 __global__ __launch_bounds__(256) void sample_extract_kernel(const uint32_t* __restrict__ trlwe, int N, uint32_t rows,
-                                                             uint32_t K, int per_block, uint32_t* __restrict__ out) {
-  for (int q = 0; q < per_block; q++) {
-    const uint32_t s = blockIdx.x * per_block + q;
+                                                             uint32_t K, uint32_t* __restrict__ out) {
+  for (int q = 0; q < PER_BLOCK; q++) {
+    const uint32_t s = blockIdx.x * PER_BLOCK + q;
     if (s >= rows) return;
     const uint32_t b = s / K;
     const int i = static_cast<int>(s - b * K);
@@ -2718,9 +2719,15 @@ int launch_sample_extract(int32_t N, const uint32_t* trlwe, int64_t B, int32_t K
     // a sample per block while all blocks are resident at once (8 per CU, 256
     // CUs) and at N = 4096 (60 x 4096 samples 703 us, four per block 866),
     // else four (N = 1024, 216 x 1024 samples 193 us, one per block 229)
-    const int per_block = rows <= 2048 || N > 2048 ? 1 : 4;
-    hipLaunchKernelGGL(sample_extract_kernel, dim3(static_cast<unsigned>((rows + per_block - 1) / per_block)), dim3(256),
-                       0, st, trlwe, N, static_cast<uint32_t>(rows), static_cast<uint32_t>(K), per_block, out);
+    auto launch = [&](auto PER_BLOCK) {
+      constexpr int per_block = decltype(PER_BLOCK)::value;
+      hipLaunchKernelGGL(sample_extract_kernel<per_block>, dim3(static_cast<unsigned>((rows + per_block - 1) / per_block)),
+                         dim3(256), 0, st, trlwe, N, static_cast<uint32_t>(rows), static_cast<uint32_t>(K), out);
+    };
+    if (rows <= 2048 || N > 2048)
+      launch(std::integral_constant<int, 1>{});
+    else
+      launch(std::integral_constant<int, 4>{});
   } else {
     hipLaunchKernelGGL(sample_extract_words_kernel, dim3(static_cast<unsigned>((rows * (N + 1) + 255) / 256)), dim3(256),
                        0, st, trlwe, N, B, K, out);
