@@ -2590,7 +2590,9 @@ int launch_keyswitch(const tfhe_eval_key* ek, const uint32_t* in, uint32_t* out,
       hipLaunchKernelGGL(keyswitch_mfma_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(KSM_THREADS), 0, st,
                          in, reinterpret_cast<const i32x4*>(ek->ksk_mfma), out, p.n, p.N, B, mode, bits, gate_begin, g);
     }
-  } else if (p.ks_t * (1 << p.ks_basebit) <= 32)
+    return launch_status("keyswitch_mfma_kernel");
+  }
+  if (p.ks_t * (1 << p.ks_basebit) <= 32)
     hipLaunchKernelGGL((keyswitch_kernel<32>), grid, dim3(KS_COLS), 0, st, in, ek->ksk, out, p.n, p.N,
                        p.ks_t, p.ks_basebit, B, mode, bits, gate_begin);
   else
@@ -2728,11 +2730,11 @@ int launch_sample_extract(int32_t N, const uint32_t* trlwe, int64_t B, int32_t K
       launch(std::integral_constant<int, 1>{});
     else
       launch(std::integral_constant<int, 4>{});
-  } else {
-    hipLaunchKernelGGL(sample_extract_words_kernel, dim3(static_cast<unsigned>((rows * (N + 1) + 255) / 256)), dim3(256),
-                       0, st, trlwe, N, B, K, out);
+    return launch_status("sample_extract_kernel");
   }
-  return launch_status("sample_extract_kernel");
+  hipLaunchKernelGGL(sample_extract_words_kernel, dim3(static_cast<unsigned>((rows * (N + 1) + 255) / 256)), dim3(256),
+                     0, st, trlwe, N, B, K, out);
+  return launch_status("sample_extract_words_kernel");
 }
 
 int launch_negacyclic_mul(const tfhe_eval_key* ek, const int32_t* d, const uint32_t* b, uint32_t* c,

@@ -255,3 +255,17 @@ def test_digit_positions_are_scalars_or_declared_per_lane(tmp_path):
     shared = {f"blind_rotate_team_kernelILi{logn}ELi{l}E" for logn in (8, 9) for l in (2, 3)}
     assert {m for k in seen["per lane"] for m in re.findall(r"blind_rotate_team_kernelILi\d+ELi\dE", k)} == shared
     assert any("blind_rotate_team_kernelILi10E" in k for k in seen["scalar"])
+
+
+@pytest.mark.parametrize("N,kernel", [(128, "sample_extract_words_kernel"), (256, "sample_extract_kernel")])
+def test_a_failed_launch_names_its_kernel(N, kernel):
+    """Without a GPU every launch fails; the message names the kernel that
+    was to run (nothing reads the buffers)."""
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("a GPU is present")
+    L = tfhe.lib()
+    x, out = np.zeros(2 * N, np.uint32), np.zeros(N + 1, np.uint32)
+    rc = L.tfhe_sample_extract_batch(N, x.ctypes.data, 1, 1, out.ctypes.data, None)
+    assert rc == tfhe.TFHE_EHIP
+    assert L.tfhe_last_error().decode().startswith(f"{kernel} launch failed")
