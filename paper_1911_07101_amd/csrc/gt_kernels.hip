@@ -2110,7 +2110,12 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
   }();
   const BufTable twist{__builtin_amdgcn_make_buffer_rsrc(const_cast<double2*>(tw_g + 2 * NC), 0, NC * 16, 0x00020000)};
   __syncthreads();
-  double2* scr = s_scr + slot * Lay::SCR;
+  // (by a uniform slot where each wave holds one output: 3 registers spilled
+  // and none read again inside the loops, instead of 6 with two read per
+  // coefficient, which cost coefficients of few rows more than the key points
+  // requested early gained: t = 2, 16 outputs of 100 samples, n = 120
+  // 35.5 -> 34.5 us)
+  double2* scr = s_scr + (T == 64 && CPB > 1 ? __builtin_amdgcn_readfirstlane(slot) : slot) * Lay::SCR;
 
   const int vals = (1 << basebit) - 1, R = t_digits * vals, prec = t_digits * basebit;
   const uint32_t round = 1u << (31 - prec);  // prec <= 16
@@ -2152,10 +2157,11 @@ __global__ __launch_bounds__((BrCfg<LOGN, 2, WPB>::THREADS), (BrCfg<LOGN, 2, WPB
       for (int v = 1; v <= vals; v++) {
         const uint32_t row = static_cast<uint32_t>((j * vals + v - 1) * O * NC) * 16u;
         // the first output's key points are requested before the transform
-        // (with a point's two rounded words in one register there is room for
-        // them at two waves per SIMD too: 8 packings 0.300 -> 0.283 ms, 216
-        // 6.40 -> 6.30 ms; a block barrier per digit or row, which holds the
-        // waves to the same key lines, cost 3 % and 14 %)
+        // (a point's two rounded words share a register for that; at two waves
+        // per SIMD 3 registers are spilled all the same, outside the loops:
+        // 8 packings 0.300 -> 0.283 ms, 216 6.40 -> 6.30 ms; a block barrier per
+        // digit or row, which holds the waves to the same key lines, cost 3 %
+        // and 14 %)
         double2 w[E];
 #pragma unroll
         for (int e = 0; e < E; e++) w[e] = load_b128(kr, voff, row + static_cast<uint32_t>(e * T * 16));
@@ -2677,8 +2683,9 @@ int launch_pack_fft_blocks(const tfhe_eval_key* ek, const uint32_t* lwe, int32_t
 template <int LOGN>
 int launch_pack_fft(const tfhe_eval_key* ek, const uint32_t* lwe, int32_t Z, uint32_t* out, int64_t B,
                     hipStream_t st) {
-  // (blocks of 8 waves at N < 1024 would spill registers: one-wave blocks
-  // there hold 64 / T outputs each)
+  // (blocks of 8 waves at N < 1024, with several outputs per wave, would spill
+  // 14 to 20 registers, some of them inside the loop over rows: one-wave blocks
+  // there, which hold 64 / T outputs each)
   if constexpr (LOGN == 10)
     if (B >= 8) return launch_pack_fft_blocks<8, LOGN>(ek, lwe, Z, out, B, st);
   return launch_pack_fft_blocks<1, LOGN>(ek, lwe, Z, out, B, st);
