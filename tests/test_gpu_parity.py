@@ -246,9 +246,11 @@ def test_blind_rotate_extract_three_key_parts(torch, N):
 def test_one_wave_kernel_ring_sizes_and_gadgets(torch, N, l, bg_bit):
     """The blind rotation with two key parts at N = 256, 512 and 1024 (N/16
     lanes per ciphertext) for gadgets other than the default: a small batch
-    (every sample checked) and one that fills blocks of 8 waves on every CU
+    (every sample checked; with two digits it takes a block per ciphertext,
+    else blocks of one wave) and one that fills blocks of 8 waves on every CU
     plus a ragged block (spread rows checked), with an arbitrary test
-    polynomial, bit for bit against the oracle."""
+    polynomial, bit for bit against the oracle.  (Blocks of one wave with two
+    digits: test_team_blocks_match_wave_blocks.)"""
     params = dict(n=8, N=N, l=l, bg_bit=bg_bit, ks_t=8, ks_basebit=2, alpha_lwe=2 ** -15, alpha_bk=2 ** -25)
     assert tfhe.tfhe_transform_error_bound(params)[0] == 2
     sk, ek, ok = keys_for(f"ring{N}_l{l}_bg{bg_bit}", torch, params=params, seed=0x1024 + N + 16 * l + bg_bit)
@@ -267,15 +269,19 @@ def test_split_kernel_digit_paths(torch, l, bg_bit):
     """The two-wave blind rotation at N = 2048 with two key parts for other
     gadgets: digits recomputed from the accumulator for each digit (l != 2 or
     Bg > 2^10) and the second digit kept packed from the first (l = 2,
-    Bg = 2^9), in blocks of one ciphertext (a small batch, every sample
-    checked) and of four (1027 samples, spread rows checked), with an
-    arbitrary test polynomial, bit for bit against the oracle."""
+    Bg = 2^9), with an arbitrary test polynomial, bit for bit against the
+    oracle: a small batch (every sample checked; one wave per SIMD, or teams
+    with two digits), one of two per CU and one more, which runs as blocks of
+    one ciphertext at two waves per SIMD, and one of four per CU and three
+    more in blocks of four (spread rows checked)."""
     params = dict(n=8, N=2048, l=l, bg_bit=bg_bit, ks_t=8, ks_basebit=2, alpha_lwe=2 ** -15, alpha_bk=2 ** -25)
     assert tfhe.tfhe_transform_error_bound(params)[0] == 2
     sk, ek, ok = keys_for(f"split_l{l}_bg{bg_bit}", torch, params=params, seed=0x5117 + 16 * l + bg_bit)
     rng = np.random.default_rng(47 + l * bg_bit)
     tv = rng.integers(0, M32, 2048, dtype=np.uint64).astype(np.uint32)
-    for B, rows in ((5, np.arange(5)), (1027, np.linspace(0, 1026, 8).astype(int))):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for B in (5, 2 * cus + 1, 4 * cus + 3):
+        rows = np.arange(5) if B == 5 else np.linspace(0, B - 1, 8).astype(int)
         x = rng.integers(0, M32, (B, 9), dtype=np.uint64).astype(np.uint32)
         say(f"split kernel l={l} bg_bit={bg_bit} B={B}")
         got = tfhe.to_host(tfhe.tfhe_bootstrap_extract_batch(ek, tfhe.to_device(x), tfhe.to_device(tv)))
@@ -859,14 +865,14 @@ def test_tfhe128_nand_4096(torch):
 
 
 def test_block_shapes_for_small_batches(torch):
-    """A batch that four one-wave blocks per CU hold (N = 1024: up to 1024
-    gates) runs in blocks of one wave, a larger one in blocks of 8; at
-    N = 2048 up to two one-ciphertext blocks per CU (512 lookups) run one
-    wave per SIMD, up to three (768) with two, else blocks of four
-    ciphertexts, whose partly filled last round runs as one-ciphertext
-    blocks of either kind (1102 = 1024 + 78, 1600 = 1024 + 576).  Both sides
-    of each boundary, with a ragged last block, give the same samples as the
-    full batch, and the last sample of each size matches the oracle."""
+    """The shapes of a launch by its batch, at 256 CUs.  N = 1024: a block per
+    ciphertext (7, 600 gates), blocks of one wave (1024), those and a round of
+    teams (1025), blocks of 8 waves and a last round of teams (2100 = 2048 +
+    52).  N = 2048: teams (100, 512, 768 lookups), blocks of one ciphertext
+    (513), of four (769), and of four with a last round of teams (1102 = 1024
+    + 78) or of one-ciphertext blocks (1600 = 1024 + 576).  Every size gives
+    the same samples as the largest, and the last sample of each matches the
+    oracle."""
     for name, sizes in (("tfhe128_nand", (2100, 1025, 1024, 600, 7)),
                         ("lut3_n2048", (1600, 1102, 769, 768, 513, 512, 100))):
         cfg = wl.CONFIGS[name]

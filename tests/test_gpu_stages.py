@@ -136,12 +136,15 @@ def key_row(p, pattern, ok):
 KEY_ROW_PATTERNS = ("parts_neg", "parts_pos", "parts_mixed", "alternating", "eval_key_row")
 
 
-@pytest.mark.parametrize("cfg_name", ["tfhe128_nand", "lut3_n2048"])
+@pytest.mark.parametrize("cfg_name,B", [("tfhe128_nand", 4096), ("tfhe128_nand", 1000), ("tfhe128_nand", 250),
+                                        ("lut3_n2048", 1027), ("lut3_n2048", 600), ("lut3_n2048", 250), ("toy", 37)])
 @pytest.mark.parametrize("pattern", KEY_ROW_PATTERNS)
-def test_one_cmux_worst_case(torch, cfg_name, pattern):
-    """One CMux at the timed shapes (4096 accumulators at N = 1024, 8-wave
-    blocks; 1027 at N = 2048, blocks of four ciphertexts and a tail of
-    one-ciphertext blocks), bit for bit against the oracle's CMux.  The
+def test_one_cmux_worst_case(torch, cfg_name, B, pattern):
+    """One CMux in every launch shape at 256 CUs (N = 1024: 4096 accumulators
+    in 8-wave blocks, 1000 in one-wave blocks, 250 a block each; N = 2048:
+    1027 in blocks of four ciphertexts with a last round of teams, 600 in
+    one-ciphertext blocks, 250 in teams; N = 256: 37 a block each), bit for
+    bit against the oracle's CMux.  The
     first accumulators rotate by N with every coefficient of both
     polynomials chosen so that every gadget digit is -Bg/2 (the largest
     magnitude), then every digit Bg/2 - 1, then digits alternating between
@@ -153,7 +156,6 @@ def test_one_cmux_worst_case(torch, cfg_name, pattern):
     p = wl.CONFIGS[cfg_name]["params"]
     N, l, bg = p["N"], p["l"], p["bg_bit"]
     sk, ek, ok = keys_for(cfg_name)
-    B = {"tfhe128_nand": 4096, "lut3_n2048": 1027}[cfg_name]
     rng = np.random.default_rng(list(KEY_ROW_PATTERNS).index(pattern) + N)
     half = 1 << (bg - 1)
     d_min, d_max = digit_word(p, -half), digit_word(p, half - 1)
