@@ -2459,12 +2459,15 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
     return launch_br<LOGN, S>(ek, ws_tail(ek, ws, io, head), testvec, tail, st, io_tail(ek, io, head));
   } else if constexpr (T == 128) {
     if constexpr (S == 2) {
-      // a team per ciphertext, one block per CU: up to 256 lookups 4.9 against
-      // 11.0 ms (n = 750), 512 9.8 against 12.5; a third round when it is two
-      // thirds full (513 15.6 against 15.6 with one-ciphertext blocks, 600 15.4
-      // against 15.1, 700 14.5 against 15.4, 768 14.4 against 16.4)
+      // a team per ciphertext, one block per CU: up to 256 lookups 4.8 against
+      // 11.0 ms (n = 750), 512 9.6 against 12.5; a third round when it is half
+      // full.  A fuller third round is the shorter one (for a reason that has
+      // not been found; one-ciphertext blocks take about the same for all):
+      // 513 15.3 against 15.6 ms with those, 544 15.4 against 15.2, 600 14.9
+      // against 15.2, 640 14.8 against 15.2, 682 14.6 against 15.1, 768 14.4
+      // against 16.2; half full is where the gain exceeds what runs differ by
       const int64_t third = B - 2 * cus;
-      const bool team = third <= 0 || (third <= cus && 3 * third >= 2 * cus);
+      const bool team = third <= 0 || (third <= cus && 2 * third >= cus);
       if (team && ek->p.l == 2) return launch_br_split_team<LOGN, 2>(ek, ws, testvec, B, st, io);
     }
     // blocks of one ciphertext: one wave per SIMD while two per CU hold the

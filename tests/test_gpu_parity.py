@@ -927,6 +927,26 @@ def test_team_blocks_match_wave_blocks(torch, N, l, bg_bit, per_cu):
     assert np.array_equal(full[idx], oracle.bootstrap_no_ks(ok, x[idx], tv))
 
 
+def test_third_round_of_teams(torch):
+    """N = 2048, more than two ciphertexts per CU: one-ciphertext blocks below
+    two and a half, teams from there to three, with the same samples on both
+    sides of the line and the oracle's at the edges."""
+    params = dict(n=5, N=2048, l=2, bg_bit=10, ks_t=8, ks_basebit=2, alpha_lwe=2 ** -15, alpha_bk=2 ** -25)
+    sk, ek, ok = keys_for("third", torch, params=params, seed=0x741D)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    line = 2 * cus + (cus + 1) // 2
+    rng = np.random.default_rng(cus)
+    tv = rng.integers(0, M32, 2048, dtype=np.uint64).astype(np.uint32)
+    x = rng.integers(0, M32, (line, 6), dtype=np.uint64).astype(np.uint32)
+    xd, tvd = tfhe.to_device(x), tfhe.to_device(tv)
+    run = lambda B: tfhe.to_host(tfhe.tfhe_bootstrap_extract_batch(ek, xd[:B], tvd))
+    say(f"third round of teams, line at {line}")
+    full = run(line)
+    assert np.array_equal(run(line - 1), full[:-1])
+    idx = np.array([0, cus, 2 * cus, line - 1])
+    assert np.array_equal(full[idx], oracle.bootstrap_no_ks(ok, x[idx], tv))
+
+
 @pytest.mark.parametrize("N,l,bg_bit,round_cu,tails_cu", [(256, 3, 7, 32, (0, 8, 16)), (512, 2, 9, 16, (0, 4, 8)),
                                                           (1024, 3, 7, 8, (0, 3, 4, 5)), (1024, 2, 9, 8, (0, 3, 4, 5)),
                                                           (2048, 2, 10, 4, (0, 2, 3))])
