@@ -1192,7 +1192,8 @@ struct BrTeamCfg {
   static constexpr int PF = 3;        // key rows requested one CMux ahead
   static constexpr int LDS_BYTES =
       NC * 16 + (NC - 1) * 16 + NC * 16 + 2 * COPIES * NR * 4 + (R + O) * SCR * 16 + MAX_N * 2;
-  // waves per SIMD of the blocks that the LDS lets share a CU
+  // waves per SIMD of the blocks that the LDS lets share a CU (N = 512, l = 3:
+  // 2 registers are spilled, outside the loop)
   static constexpr int MIN_WAVES = 160 * 1024 / LDS_BYTES * (THREADS / 64) > 4 ? 2 : 1;
   static_assert(LDS_BYTES <= 160 * 1024, "block exceeds the CU's LDS");
 };
@@ -2423,12 +2424,16 @@ int launch_br(const tfhe_eval_key* ek, const Workspace& ws, const uint32_t* test
   auto blocks = [&](int64_t b, int cpb) { return (b + cpb - 1) / cpb; };
   if constexpr (T <= 64) {
     if constexpr (S == 2) {
-      // a team per ciphertext while that is the faster: rounds of one block
-      // per CU at N = 1024 (l = 3, n = 630: 256 gates 2.65 against 8.95 ms with
-      // one-wave blocks, 512 5.05 against 9.0, 768 7.5 against 10.1, 1024
-      // 10.05 against 10.04), of two at 512 (n = 100: 512 gates 0.35 against
-      // 1.42 ms, 1024 1.30 against 1.43) and of four at 256 (n = 64: 1024 gates
-      // 0.32 against 0.72 ms, 2048 0.62 against 0.79, 4096 1.17 against 0.91)
+      // a team per ciphertext while that is the faster.  Its rounds are of one
+      // block per CU at N = 1024 (l = 3, n = 630: 256 gates 2.65 against 8.95 ms
+      // with one-wave blocks, 512 5.05 against 9.0, 768 7.5 against 10.1, 1024
+      // 10.05 against 10.04; l = 2, n = 120: 256 0.42 against 1.31, 512 0.84
+      // against 1.32, 768 1.25 against 1.43), of two at 512 (n = 100, l = 3:
+      // 512 0.45 against 1.41 ms, 1024 0.88 against 1.43; l = 2: 0.33 against
+      // 1.09, 0.65 against 1.10) and, by their LDS, of three at 256 with l = 3
+      // (n = 64: 768 0.24 against 0.72 ms, 2048 0.69 against 0.77) and of four
+      // with l = 2 (1024 0.20 against 0.57, 2048 0.39 against 0.61; 4096 would
+      // take two such, 0.77 against 0.72)
       constexpr int64_t kPerCu = LOGN == 10 ? 3 : LOGN == 9 ? 4 : 8;
       if (B <= kPerCu * cus) {
         if (ek->p.l == 3) return launch_br_team<LOGN, 3>(ek, ws, testvec, B, st, io);
