@@ -1170,12 +1170,13 @@ __global__ __launch_bounds__((BrSplitCfg<LOGN, S, WPB, SW>::THREADS),
 // SIMD to itself: 33,000 clocks at N = 1024, l = 3, of which 15,000 issue
 // arithmetic (a lone wave issues a 32-bit instruction every 8 clocks and LDS
 // writes at 38 bytes per clock).  Here the chain is one forward and one
-// inverse transform and 2l products: 9,900 clocks (digits 640, forward 2250,
-// its write and the wait for the two waves that share a SIMD 1600, products
-// 2000, inverse 1900, update 1300).  Up to 256 gates at n = 630: 8.95 ->
-// 2.65 ms; 16 gates at n = 64, N = 256: 0.72 -> 0.18 ms.  What bounds it is
-// LDS traffic (about 5900 clocks of it per CMux, two thirds of them writes,
-// which run at 80 bytes per clock against 250 for reads) at six waves in step.
+// inverse transform and 2l products: 9,800 clocks (digits 650, forward 2250,
+// its write and the wait for the two waves that share a SIMD 1500, products
+// 2100, inverse 2000, update 1050, the last barrier 200).  Up to 256 gates at
+// n = 630: 8.95 -> 2.65 ms; 16 gates at n = 64, N = 256: 0.72 -> 0.18 ms.  No
+// unit is full: of a CMux's clocks the LDS is busy 46 %, the return of key
+// points 50 %, the vector units 36 %, and the LDS return queue is full 61 %;
+// six waves in step wait for each phase's LDS accesses.
 // The key is requested up to one CMux ahead, a row at a time between other
 // work: 24 loads in a row held their wave up for 900 clocks, and rows
 // requested when needed for 1500.
@@ -1371,10 +1372,12 @@ __global__ __launch_bounds__((BrTeamCfg<LOGN, L>::THREADS), (BrTeamCfg<LOGN, L>:
 // digit polynomial r, wave 2 o + h the products, the inverse and the last
 // inverse stage's slice of output o.  (The tables fill the LDS: the rows'
 // space serves the inverse transforms too, after one more barrier.)  A CMux
-// takes 15,400 clocks against 34,500 of the two-wave kernel alone on its CU;
-// up to 256 lookups at n = 750 11.0 -> 4.9 ms.  Bounds: LDS traffic (about
-// 10,000 clocks) and the 880 vector instructions of each of the two waves on
-// a SIMD; without its key loads it would take 14,800.
+// takes 15,300 clocks against 34,500 of the two-wave kernel alone on its CU
+// (digits 1950, forward 2350, wait 2650, products 1300, inverse 3100, last
+// stage and update 3550, barrier 400); up to 256 lookups at n = 750 11.0 ->
+// 4.8 ms.  The LDS is busy 50 % of them and its return queue full 74 %, the
+// vector units 44 % (845 instructions of each of the two waves on a SIMD), the
+// return of key points 38 %.
 template <int LOGN, int L>
 struct BrSplitTeamCfg {
   using Lay = RingLayout<LOGN, 2>;
@@ -1743,10 +1746,13 @@ __global__ __launch_bounds__(64) void keyswitch_kernel(const uint32_t* __restric
 // partial sum mod 2^32 to an output that keyswitch_init_kernel set to
 // (0, b), so the result does not depend on the order of the additions; a
 // block that covers the whole range writes (0, b) minus its sums itself.
-// What bounds it at large batches is power: the same product instructions
-// alone reach 4.7 POP/s on zeros, 3.6 to 3.9 on random bytes and 3.2 with four
-// byte permutations beside each; the kernel runs at 2.1 to 2.2.  Blocks of
-// 256 samples, which halve the key's traffic, took the same time.
+// Two things hold it at 2.2 POP/s at large batches (207,360 samples to n = 630,
+// 11.6 ms): under these products the clock falls to about 1.7 GHz (the same
+// instructions alone reach 4.7 POP/s on zeros, 3.6 to 3.9 on random bytes and
+// 3.2 with four byte permutations beside each), and at that clock the matrix
+// cores are busy 64 % of the time, the return of key tiles and inputs through
+// L1 89 %.  Blocks of 256 samples, which halve the key's traffic, took the same
+// time.
 constexpr int KSM_WAVES = 4;                      // waves per block
 constexpr int KSM_NB = 2;                         // 32-column blocks per block (ksk_mfma_nb pads to it)
 constexpr int KSM_THREADS = 64 * KSM_WAVES;
